@@ -7,13 +7,19 @@
 
 namespace capred {
 
-constexpr int kBeliefThreads = 256;
-constexpr int kDeltaSlots = 1024;  // Delta of one transition for a chunk of goals x all controls
-                                   // (8 KiB: the update fits beside the rollout blocks of a busy CU)
+constexpr int kBeliefThreads = 256;       // threads of an update block of a plan
+constexpr int kBeliefThreadsWide = 1024;  // threads of the single-human entry point's blocks
+constexpr int kMaxChunkT = 64;     // transitions per chunk
 
+// NT threads per block.  The Delta buffer holds four values per thread: 8 KiB
+// in a plan, where the update fits beside the rollout blocks of a busy CU.
+template <int NT>
 struct BeliefShared {
-  double dl[kDeltaSlots];
-  double red[kBeliefThreads / 64];
+  static constexpr int kDeltas = 4 * NT;
+  BeliefModel m;           // staged: lanes read its tables by their own index
+  double dl[kDeltas];      // Delta of a chunk of transitions x goals x controls
+  double part[CAP_MAX_J];  // sums of the (pair, share of the transitions) tasks
+  int ks[kMaxChunkT];
 };
 
 // Control recovered from one observed transition (the nearest control):
@@ -173,96 +179,156 @@ __device__ __forceinline__ double policy_delta(const GoalOffset& o, float sx, fl
   return df_to_double(df_div(n, df_add(d, o.D)));
 }
 
-// log pi(u* | z; beta, g) from the U values -Delta_u: l_u = -beta Delta_u and
-// log pi = (l_{u*} - max l) - log sum exp(l - max l), FP64, one pass with a
-// running maximum.
-__device__ __forceinline__ double policy_term_from(const double* dl, int U, int ks, double beta) {
-  double mx = -INFINITY, s = 0.0, lks = 0.0;
-  for (int u = 0; u < U; ++u) {
-    const double l = -beta * dl[u];
-    if (u == ks) lks = l;
-    if (l > mx) {
-      s = s * exp(mx - l) + 1.0;
-      mx = l;
-    } else {
-      s += exp(l - mx);
-    }
-  }
-  return (lks - mx) - log(s);
+// Sum and minimum over the L = 8 or 16 lanes of a group (aligned), in every
+// lane, by DPP moves: neighbours, pairs, then mirrored halves of 8 and of 16.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+template <int L>
+__device__ __forceinline__ double lanes_sum(double v) {
+  v += dpp_move<kDppXor1>(v);
+  v += dpp_move<kDppXor2>(v);
+  v += dpp_move<kDppHalfMirror>(v);
+  if constexpr (L == 16) v += dpp_move<kDppMirror>(v);
+  return v;
+}
+template <int L>
+__device__ __forceinline__ double lanes_min(double v) {
+  v = fmin(v, dpp_move<kDppXor1>(v));
+  v = fmin(v, dpp_move<kDppXor2>(v));
+  v = fmin(v, dpp_move<kDppHalfMirror>(v));
+  if constexpr (L == 16) v = fmin(v, dpp_move<kDppMirror>(v));
+  return v;
 }
 
-__device__ __forceinline__ double block_reduce(double v, bool is_max, double* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double x = __shfl_xor(v, o, 64);
-    v = is_max ? fmax(v, x) : v + x;
-  }
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double r = red[0];
-  for (int w = 1; w < nw; ++w) r = is_max ? fmax(r, red[w]) : r + red[w];
-  return r;
+// log pi(u* | z; beta, g) from the U values Delta_u, by L lanes together (lane
+// `sub` takes every L-th control): l_u = -beta Delta_u and
+// log pi = (l_{u*} - max l) - log sum exp(l - max l), FP64.  The largest logit
+// belongs to the smallest Delta (beta > 0, rounding is monotone).
+template <int L>
+__device__ __forceinline__ double policy_term_lanes(const double* dl, int U, int ks, double beta,
+                                                    int sub) {
+  double dmin = INFINITY;
+  for (int u = sub; u < U; u += L) dmin = fmin(dmin, dl[u]);
+  const double mx = -beta * lanes_min<L>(dmin);
+  double s = 0.0;
+  for (int u = sub; u < U; u += L) s += exp(-beta * dl[u] - mx);
+  return (-beta * dl[ks] - mx) - log(lanes_sum<L>(s));
 }
 
-// One human's update: log_belief[j] += sum_t ell_t(j), renormalised by one
-// FP64 log-sum-exp.  Per transition and chunk of goals, the threads first
-// evaluate every (goal, control) Delta once into LDS, then every (goal, beta)
-// term from them; thread tid owns pairs j = tid + r blockDim.x and adds their
-// terms in transition order, so all sums run in a fixed order (bitwise
-// reproducible).
-__device__ void belief_update_block(const BeliefModel& m, const float* __restrict__ obs,
-                                    int n_obs, double* __restrict__ log_belief,
-                                    double* __restrict__ belief_out, BeliefShared& sh) {
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int G = m.G, B = m.B, U = m.U, J = G * B;
-  const int gchunk = max(1, kDeltaSlots / U);
-  constexpr int kPerThread = CAP_MAX_J / kBeliefThreads;
-  double acc[kPerThread];
-#pragma unroll
-  for (int r = 0; r < kPerThread; ++r) acc[r] = 0.0;
-  for (int t = 0; t < n_obs; ++t) {
-    const float zx = obs[2 * t], zy = obs[2 * t + 1];
-    const int ks = recover_control(m, obs[2 * t + 2] - zx, obs[2 * t + 3] - zy);
-    if (ks < 0) continue;  // no displacement: no information (uniform across the block)
-    for (int g0 = 0; g0 < G; g0 += gchunk) {
-      const int gn = min(gchunk, G - g0);
-      for (int item = tid; item < gn * U; item += nthr) {
-        const int gl = item / U, u = item - gl * U;
-        const GoalOffset o = goal_offset(zx, zy, m.gx[g0 + gl], m.gy[g0 + gl]);
+// Adds sum_t ell_t(g, b) of the goals [g0, g1) and betas [b0, b1) to
+// log_belief (not yet normalised).  Every Delta of a chunk of transitions x
+// goals x controls is evaluated once, in parallel, into LDS; then groups of L
+// lanes take the tasks (pair, share of the transitions), one policy term at a
+// time.  What bounds it is the latency of dependent FP64 work, so every level
+// (transitions, goals, pairs, controls) is spread over the lanes: with one
+// thread per pair running its controls' exponentials one after another and the
+// transitions in series, 40 observations of a 96-control model over 21 goals x
+// 5 betas took 2524 us.  Each sum runs in a fixed order for given sizes and
+// block size (bitwise reproducible).  Now 13.0 us for that history (one block
+// per pair) and 8.4 us for 10 observations of 8 controls over 2 goals x 4
+// betas (38.7 us before), most of it the round trips and chains of one term.
+template <int NT, int L>
+__device__ __forceinline__ void belief_terms(const float* __restrict__ obs,
+                                             int n_obs, double* log_belief, int g0,
+                                             int g1, int b0, int b1, BeliefShared<NT>& sh) {
+  const BeliefModel& m = sh.m;
+  const int tid = threadIdx.x;
+  const int B = m.B, U = m.U, nb = b1 - b0;
+  constexpr int kGroups = NT / L;
+  const int grp = tid / L, sub = tid % L;
+  const int gstep = max(1, min(g1 - g0, sh.kDeltas / U));
+  for (int gb = g0; gb < g1; gb += gstep) {
+    const int gn = min(gstep, g1 - gb), pairs = gn * nb;
+    const int tstep = min(kMaxChunkT, sh.kDeltas / (gn * U));
+    const int shares = max(1, min(min(n_obs, tstep), kGroups / pairs));
+    const int tasks = pairs * shares;   // at most max(pairs, kGroups) <= CAP_MAX_J
+    for (int k = tid; k < tasks; k += NT) sh.part[k] = 0.0;
+    for (int t0 = 0; t0 < n_obs; t0 += tstep) {
+      const int tn = min(tstep, n_obs - t0);
+      for (int i = tid; i < tn; i += NT) {
+        const float* z = obs + 2 * (t0 + i);
+        sh.ks[i] = recover_control(m, z[2] - z[0], z[3] - z[1]);
+      }
+      for (int item = tid; item < tn * gn * U; item += NT) {
+        const int tg = item / U, u = item - tg * U;
+        const int tl = tg / gn, gl = tg - tl * gn;
+        const float zx = obs[2 * (t0 + tl)], zy = obs[2 * (t0 + tl) + 1];
+        const GoalOffset o = goal_offset(zx, zy, m.gx[gb + gl], m.gy[gb + gl]);
         sh.dl[item] = policy_delta(o, m.sx[u], m.sy[u]);
       }
       __syncthreads();
-#pragma unroll
-      for (int r = 0; r < kPerThread; ++r) {
-        const int j = tid + r * nthr, g = j / B;
-        if (j < J && g >= g0 && g < g0 + gn)
-          acc[r] += policy_term_from(sh.dl + (g - g0) * U, U, ks, (double)m.beta[j - g * B]);
+      for (int k = grp; k < tasks; k += kGroups) {
+        const int q = k / pairs, p = k - q * pairs, gl = p / nb;
+        const double beta = (double)m.beta[b0 + p - gl * nb];
+        double acc = 0.0;
+        for (int tl = q; tl < tn; tl += shares) {
+          const int ks = sh.ks[tl];
+          if (ks >= 0)   // below 1e-9 m: no information
+            acc += policy_term_lanes<L>(sh.dl + (tl * gn + gl) * U, U, ks, beta, sub);
+        }
+        if (sub == 0) sh.part[k] += acc;
       }
       __syncthreads();
     }
+    for (int p = tid; p < pairs; p += NT) {
+      const int gl = p / nb, j = (gb + gl) * B + b0 + p - gl * nb;
+      double s = 0.0;
+      for (int q = 0; q < shares; ++q) s += sh.part[q * pairs + p];
+      log_belief[j] += s;
+    }
+    __syncthreads();
   }
-  double v[kPerThread];
+}
+
+template <int NT>
+__device__ __forceinline__ void belief_terms_any(const BeliefModel& m, const float* obs, int n_obs,
+                                                 double* log_belief, int g0, int g1, int b0,
+                                                 int b1, BeliefShared<NT>& sh) {
+  // stage the model first: its tables lie in the kernel's arguments or in a
+  // slot's descriptor, and each dependent read of those costs a round trip
+  static_assert(sizeof(BeliefModel) % 4 == 0, "copied as words");
+  for (int i = threadIdx.x; i < (int)(sizeof(BeliefModel) / 4); i += NT)
+    reinterpret_cast<uint32_t*>(&sh.m)[i] = reinterpret_cast<const uint32_t*>(&m)[i];
+  __syncthreads();
+  if (m.U <= 8) belief_terms<NT, 8>(obs, n_obs, log_belief, g0, g1, b0, b1, sh);
+  else belief_terms<NT, 16>(obs, n_obs, log_belief, g0, g1, b0, b1, sh);
+}
+
+// Renormalises the J entries of log_belief by one FP64 log-sum-exp and writes
+// belief_out = exp(log_belief) (nullable).  One wavefront (the caller's first;
+// the others return): at most eight pairs per lane, and no barrier between the
+// steps of a chain whose latency is all there is to pay.
+__device__ __forceinline__ void belief_normalize(int J, double* log_belief, double* belief_out) {
+  constexpr int kPerLane = CAP_MAX_J / 64;
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  double v[kPerLane];
   double mx = -INFINITY;
 #pragma unroll
-  for (int r = 0; r < kPerThread; ++r) {
-    const int j = tid + r * nthr;
-    v[r] = j < J ? log_belief[j] + acc[r] : -INFINITY;
+  for (int r = 0; r < kPerLane; ++r) {
+    const int j = lane + r * 64;
+    v[r] = j < J ? log_belief[j] : -INFINITY;
     mx = fmax(mx, v[r]);
   }
-  mx = block_reduce(mx, true, sh.red);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
   double s = 0.0;
 #pragma unroll
-  for (int r = 0; r < kPerThread; ++r) {
-    const int j = tid + r * nthr;
-    if (j < J) s += exp(v[r] - mx);
-  }
-  s = block_reduce(s, false, sh.red);
+  for (int r = 0; r < kPerLane; ++r)
+    if (lane + r * 64 < J) s += exp(v[r] - mx);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   const double lse = mx + log(s);
 #pragma unroll
-  for (int r = 0; r < kPerThread; ++r) {
-    const int j = tid + r * nthr;
+  for (int r = 0; r < kPerLane; ++r) {
+    const int j = lane + r * 64;
     if (j < J) {
       const double lb = v[r] - lse;
       log_belief[j] = lb;

@@ -29,6 +29,7 @@ namespace capred {
 constexpr int kMaxObs = 8;
 constexpr int kXcds = 8;
 constexpr int kQueueWords = kXcds;   // tile counters per ring entry, one per XCD
+                                     // (followed by one update ticket per slot)
 constexpr int kTileKinds = 3;    // P, P/2, P/4 particles per thread
 constexpr int kZeroBlocks = 2048;  // blocks of the grid clear
 
@@ -48,11 +49,13 @@ struct SlotDev {
   int32_t kt_begin[kTileKinds];  // per tile kind: tickets of earlier slots (within the kind)
   int32_t kt_first[kTileKinds];  // per tile kind: first particle of this slot's tiles
   int32_t in_union;              // 1: this slot's probabilities join the union grid
+  int32_t upd_blocks;            // blocks that share this slot's belief update
 };
 
 struct CycleHeader {
   uint32_t seed_lo, seed_hi, cycle;
   int32_t n_active, n_tiles, per_tile;
+  int32_t upd_blocks;                      // update blocks per slot in the prelude launch
   int32_t kind_begin[kTileKinds + 1];      // ticket ranges of the three tile kinds
   int32_t tile_begin[CAP_MAX_SLOTS + 1];   // per-human launches: prefix of P-sized tiles
   int32_t step_begin[CAP_MAX_SLOTS + 1];   // prefix of horizons (one work item per step)
@@ -82,25 +85,42 @@ __device__ __forceinline__ const SlotDev* slots_of(const uint8_t* base) {
 }
 
 // ---------------------------------------------------------------- kernels
-// Belief update of slot s (one block).
-__device__ __forceinline__ void update_slot(const uint8_t* __restrict__ base, int s,
-                                            BeliefShared& sh) {
+// Belief update of slot s, share `part` of its goals (upd_blocks shares, each
+// one block).  With several shares the block that finishes last (an atomic
+// ticket, set back to 0 for the next cycle) normalises; the shares write
+// disjoint pairs of log_belief, so the result does not depend on the order.
+__device__ __forceinline__ void update_slot(const uint8_t* __restrict__ base, int s, int part,
+                                            uint32_t* tickets, BeliefShared<kBeliefThreads>& sh) {
   const CycleHeader* H = reinterpret_cast<const CycleHeader*>(base);
   if (s >= H->n_active) return;
   const SlotDev& sd = slots_of(base)[s];
-  const int J = sd.bm.G * sd.bm.B;
+  const int shares = tickets ? sd.upd_blocks : 1;
+  if (part >= shares) return;
+  const int G = sd.bm.G, B = sd.bm.B, J = G * B;
+  const int g0 = (int)((int64_t)G * part / shares), g1 = (int)((int64_t)G * (part + 1) / shares);
   if (sd.reset) {
-    for (int j = threadIdx.x; j < J; j += blockDim.x) sd.log_belief[j] = -log((double)J);
+    for (int j = g0 * B + (int)threadIdx.x; j < g1 * B; j += blockDim.x)
+      sd.log_belief[j] = -log((double)J);
     __syncthreads();
   }
-  belief_update_block(sd.bm, sd.obs, sd.n_obs, sd.log_belief, const_cast<double*>(sd.rd.belief),
-                      sh);
+  belief_terms_any(sd.bm, sd.obs, sd.n_obs, sd.log_belief, g0, g1, 0, B, sh);
+  if (shares > 1) {
+    __threadfence();   // this thread's pairs before the ticket
+    __syncthreads();
+    __shared__ uint32_t ticket;
+    if (threadIdx.x == 0) ticket = atomicAdd(tickets + s, 1u);
+    __syncthreads();
+    if (ticket != (uint32_t)shares - 1u) return;
+    if (threadIdx.x == 0) tickets[s] = 0u;
+    __threadfence();   // the other shares' pairs after the ticket
+  }
+  belief_normalize(J, sd.log_belief, const_cast<double*>(sd.rd.belief));
 }
 
 __global__ void __launch_bounds__(kBeliefThreads)
     plan_update_kernel(const uint8_t* __restrict__ base, int only) {
-  __shared__ BeliefShared sh;
-  update_slot(base, only >= 0 ? only : (int)blockIdx.x, sh);
+  __shared__ BeliefShared<kBeliefThreads> sh;
+  update_slot(base, only >= 0 ? only : (int)blockIdx.x, 0, nullptr, sh);
 }
 
 // Clearing and normalising work only where a ring entry's grids can be
@@ -179,18 +199,21 @@ __global__ void __launch_bounds__(256)
   zero_items(base, queues, only, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// The start of a batched cycle in one launch: blocks [0, n_slots) update the
-// beliefs (one per slot), the rest clear the grids and reset the tile queues.
-// The two are independent, so they run side by side instead of one after the
-// other (and one launch gap fewer).
+// The start of a batched cycle in one launch: blocks [0, n_upd) update the
+// beliefs (upd_blocks per slot), the rest clear the grids and reset the tile
+// queues.  The two are independent, so they run side by side instead of one
+// after the other (and one launch gap fewer).
 __global__ void __launch_bounds__(kBeliefThreads)
     plan_prelude_kernel(const uint8_t* __restrict__ base, uint32_t* __restrict__ queues,
-                        int n_slots) {
-  __shared__ BeliefShared sh;
-  if ((int)blockIdx.x < n_slots)
-    update_slot(base, (int)blockIdx.x, sh);
-  else
-    zero_items(base, queues, -1, (int)blockIdx.x - n_slots, (int)gridDim.x - n_slots);
+                        int n_upd) {
+  __shared__ BeliefShared<kBeliefThreads> sh;
+  if ((int)blockIdx.x < n_upd) {
+    const int per = reinterpret_cast<const CycleHeader*>(base)->upd_blocks;
+    const int s = (int)blockIdx.x / per;
+    update_slot(base, s, (int)blockIdx.x - s * per, queues + kQueueWords, sh);
+  } else {
+    zero_items(base, queues, -1, (int)blockIdx.x - n_upd, (int)gridDim.x - n_upd);
+  }
 }
 
 __global__ void __launch_bounds__(256)
@@ -378,7 +401,7 @@ struct HostSlot {
 };
 
 struct Entry {
-  uint32_t* queues = nullptr;   // this entry's tile counter (device)
+  uint32_t* queues = nullptr;   // this entry's tile counters and update tickets (device)
   uint8_t* dev = nullptr;       // header + slots
   uint8_t* host = nullptr;      // pinned mirror
   hipGraphExec_t main[2] = {nullptr, nullptr};  // [shift variant]
@@ -395,7 +418,7 @@ struct cap_plan {
   cap_plan_config cfg;
   std::vector<capred::HostSlot> slots;
   std::vector<capred::Entry> ring;
-  uint32_t* queues = nullptr;   // one tile counter per ring entry (device)
+  uint32_t* queues = nullptr;   // tile counters and update tickets of every ring entry (device)
   size_t entry_bytes = 0;
   int cap_words = 0;            // LDS window words per buffer
   int grid_blocks[2] = {0, 0};  // persistent blocks per launch, per rollout variant
@@ -591,6 +614,16 @@ static void split_tiles(const int32_t* units, int n, int P, int R, int C,
   }
 }
 
+// Blocks that share one human's belief update: one while a block's Deltas (at
+// most one or two per thread) are cheaper than the ticket's round trip, then
+// about kShareDeltas of them per block, at least one goal each.
+constexpr int kShareDeltas = 2 * kBeliefThreads;
+
+static int update_shares(const BeliefModel& m, int n_obs) {
+  const int64_t deltas = (int64_t)n_obs * m.G * m.U;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(m.G, deltas / kShareDeltas));
+}
+
 static bool same_frame(const cap_grid& a, const cap_grid& b) {
   return a.x0 == b.x0 && a.y0 == b.y0 && a.cell == b.cell && a.nx == b.nx && a.ny == b.ny;
 }
@@ -604,6 +637,7 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
   H->seed_hi = (uint32_t)(seed >> 32);
   H->cycle = cycle;
   H->per_tile = p->per_tile;
+  H->upd_blocks = 1;
   int n = 0, tiles = 0, steps_total = 0, sblocks = 0, variant = 0;
   int64_t parts = 0, steps = 0;
   for (auto& hs : p->slots) {
@@ -631,6 +665,8 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
       hs.last[1] = hs.staged[2 * hs.n_staged - 1];
     }
     hs.n_staged = 0;
+    sd.upd_blocks = update_shares(sd.bm, sd.n_obs);
+    H->upd_blocks = std::max(H->upd_blocks, sd.upd_blocks);
     // the rollout starts from the newest observed position (validated at staging)
     sd.rd.X0 = (int32_t)lattice_coord((double)hs.last[0], hs.grid.x0, hs.grid.cell);
     sd.rd.Y0 = (int32_t)lattice_coord((double)hs.last[1], hs.grid.y0, hs.grid.cell);
@@ -803,9 +839,10 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
       return hip_fail(he, #call);           \
     }                                       \
   } while (0)
-  CAP_TRY(hipMalloc(&p->queues, (size_t)cfg.ring * kQueueWords * sizeof(uint32_t)));
-  CAP_TRY(hipMemset(p->queues, 0, (size_t)cfg.ring * kQueueWords * sizeof(uint32_t)));
-  for (int e = 0; e < cfg.ring; ++e) p->ring[e].queues = p->queues + (size_t)e * kQueueWords;
+  const size_t queue_words = kQueueWords + (size_t)cfg.n_slots;
+  CAP_TRY(hipMalloc(&p->queues, (size_t)cfg.ring * queue_words * sizeof(uint32_t)));
+  CAP_TRY(hipMemset(p->queues, 0, (size_t)cfg.ring * queue_words * sizeof(uint32_t)));
+  for (int e = 0; e < cfg.ring; ++e) p->ring[e].queues = p->queues + (size_t)e * queue_words;
   CAP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
   CAP_TRY(hipEventCreateWithFlags(&p->ev_update, hipEventDisableTiming));
   for (auto& en : p->ring) {
@@ -973,8 +1010,10 @@ extern "C" cap_status cap_plan_run(cap_plan* p, uint64_t seed, uint32_t cycle, v
   Entry& en = p->ring[e];
   // belief update and grid clear in one direct launch (a graph of one node
   // costs more host time), then its event, which the next cycle's stream waits on
-  hipLaunchKernelGGL(plan_prelude_kernel, dim3(p->cfg.n_slots + kZeroBlocks), dim3(kBeliefThreads),
-                     0, s, (const uint8_t*)en.dev, en.queues, p->cfg.n_slots);
+  const CycleHeader* H = reinterpret_cast<const CycleHeader*>(en.host);
+  const int n_upd = H->n_active * H->upd_blocks;
+  hipLaunchKernelGGL(plan_prelude_kernel, dim3(n_upd + kZeroBlocks), dim3(kBeliefThreads),
+                     0, s, (const uint8_t*)en.dev, en.queues, n_upd);
   CAP_HIP(hipGetLastError());
   CAP_HIP(hipEventRecord(p->ev_update, s));
   CAP_HIP(hipGraphLaunch(en.main[p->last_variant], s));
