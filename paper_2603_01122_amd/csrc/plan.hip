@@ -253,12 +253,14 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Smoothing tiles (step, band of kBandRows rows, 256 columns) of every slot
-// that asks for Gaussian-smoothed probabilities, as one index space
-// (smooth_begin prefix) walked by a persistent grid.
+// Smoothing tiles (step, 32 rows x 64 columns) of every slot that asks for
+// Gaussian-smoothed probabilities, as one index space (smooth_begin prefix)
+// walked by a persistent grid.  A tile farther than the radius from the step's
+// clear region is skipped: its counts are zero, and its probabilities are
+// still the zeros of an earlier cycle (see clear_region).
 __global__ void __launch_bounds__(kSmoothThreads)
     plan_smooth_kernel(const uint8_t* __restrict__ base, int only) {
-  extern __shared__ float tile[];
+  extern __shared__ __align__(16) float tile[];
   const CycleHeader* H = reinterpret_cast<const CycleHeader*>(base);
   const SlotDev* sl = slots_of(base);
   const int na = H->n_active;
@@ -273,20 +275,33 @@ __global__ void __launch_bounds__(kSmoothThreads)
     }
     const int s = __builtin_amdgcn_readfirstlane(lo);
     const SlotDev& sd = sl[s];
-    const int nx = sd.rd.nx, ny = sd.rd.ny;
-    const int tx = (nx + kSmoothThreads - 1) / kSmoothThreads;
-    const int ty = (ny + kBandRows - 1) / kBandRows;
+    const int nx = sd.rd.nx, ny = sd.rd.ny, r = sd.smooth_r;
+    const int tx = (nx + kBandCols - 1) / kBandCols;
+    const int per_step = smooth_tiles(ny, nx);
     const int local = b - H->smooth_begin[s];
-    const int t = local / (tx * ty);
-    const int rem = local - t * tx * ty;
+    const int t = local / per_step;
+    const int rem = local - t * per_step;
     const int by = rem / tx, bx = rem - by * tx;
+    const int y0 = by * kBandRows, x0 = bx * kBandCols;
+    const Window reg = clear_region(sd, t + 1);
+    if (reg.w == 0 || reg.h == 0 || x0 >= reg.x0 + reg.w + r || x0 + kBandCols <= reg.x0 - r ||
+        y0 >= reg.y0 + reg.h + r || y0 + kBandRows <= reg.y0 - r)
+      continue;
     const size_t plane = (size_t)ny * nx;
     float* un = sd.in_union && t + 1 <= H->union_H
                     ? H->union_out + (size_t)t * H->union_nx * H->union_ny
                     : nullptr;
-    smooth_block(sd.rd.counts + (size_t)t * plane, sd.probs + (size_t)t * plane, ny, nx,
-                 sd.smooth_r, (float)sd.rd.N, sd.smooth_w.w, by * kBandRows,
-                 bx * kSmoothThreads, tile, un);
+    const uint32_t* c = sd.rd.counts + (size_t)t * plane;
+    float* o = sd.probs + (size_t)t * plane;
+    const float Nf = (float)sd.rd.N;
+    const float* w = sd.smooth_w.w;
+    switch (smooth_bucket(r)) {
+      case 2: smooth_block<2>(c, o, ny, nx, r, Nf, w, y0, x0, tile, un); break;
+      case 3: smooth_block<3>(c, o, ny, nx, r, Nf, w, y0, x0, tile, un); break;
+      case 4: smooth_block<4>(c, o, ny, nx, r, Nf, w, y0, x0, tile, un); break;
+      case 8: smooth_block<8>(c, o, ny, nx, r, Nf, w, y0, x0, tile, un); break;
+      default: smooth_block<16>(c, o, ny, nx, r, Nf, w, y0, x0, tile, un); break;
+    }
     __syncthreads();  // the next tile rewrites `tile`
   }
 }
@@ -682,8 +697,7 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
     tiles += (int)((sd.rd.N + p->per_tile - 1) / p->per_tile);
     steps_total += sd.rd.H;
     if (sd.smooth_r > 0 && sd.probs)
-      sblocks += sd.rd.H * ((sd.rd.ny + kBandRows - 1) / kBandRows) *
-                 ((sd.rd.nx + kSmoothThreads - 1) / kSmoothThreads);
+      sblocks += sd.rd.H * smooth_tiles(sd.rd.ny, sd.rd.nx);
     parts += sd.rd.N;
     steps += (int64_t)sd.rd.N * sd.rd.H;
     ++n;

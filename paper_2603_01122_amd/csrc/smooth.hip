@@ -8,13 +8,8 @@
 // the same kernel as the 2-D one over the square window (the 2-D Gaussian
 // factorises and so does its normaliser).
 //
-// Layout on gfx950: one 256-thread block per (step, band of kBandRows output
-// rows, 256 output columns).  Pass 1 blurs the band's rows plus r halo rows
-// above and below along x straight from the uint32 grid (the 2r+1 shifted
-// loads of one row hit the same cache lines, so HBM sees each count about
-// (1 + 2r / kBandRows) times) into an LDS tile; pass 2 blurs the tile along y
-// and writes FP32 probabilities row-coalesced.  The kernel is HBM-bound:
-// 4 B read and 4 B written per cell.
+// Layout on gfx950: one 256-thread block per (step, 32 rows x 64 columns) tile
+// (smooth_block).
 #include <algorithm>
 #include <vector>
 
@@ -22,13 +17,14 @@
 
 namespace capred {
 
+template <int RM>
 __global__ void __launch_bounds__(kSmoothThreads)
 smooth_kernel(const uint32_t* __restrict__ counts, float* __restrict__ out, int ny, int nx,
               int r, float Nf, SmoothWeights W) {
-  extern __shared__ float tile[];  // [kBandRows + 2r][kSmoothThreads]
+  __shared__ __align__(16) float tile[SmoothTile<RM>::kBytes / sizeof(float)];
   const size_t plane = (size_t)ny * nx;
-  smooth_block(counts + (size_t)blockIdx.z * plane, out + (size_t)blockIdx.z * plane, ny, nx, r,
-               Nf, W.w, (int)blockIdx.y * kBandRows, (int)blockIdx.x * kSmoothThreads, tile);
+  smooth_block<RM>(counts + (size_t)blockIdx.z * plane, out + (size_t)blockIdx.z * plane, ny, nx,
+                   r, Nf, W.w, (int)blockIdx.y * kBandRows, (int)blockIdx.x * kBandCols, tile);
 }
 
 struct UnionPtrs {
@@ -77,11 +73,19 @@ extern "C" cap_status cap_smooth_occupancy(const uint32_t* counts_dev, int32_t H
     return fail(CAP_E_INVALID, "probs must not alias counts");
   SmoothWeights W;
   smooth_weights(sigma, radius, &W);
-  const dim3 grid((unsigned)((nx + kSmoothThreads - 1) / kSmoothThreads),
+  const dim3 grid((unsigned)((nx + kBandCols - 1) / kBandCols),
                   (unsigned)((ny + kBandRows - 1) / kBandRows), (unsigned)H);
-  const size_t lds = smooth_lds_bytes(radius);
-  hipLaunchKernelGGL(smooth_kernel, grid, dim3(kSmoothThreads), lds, as_stream(stream),
-                     counts_dev, probs_dev, (int)ny, (int)nx, (int)radius, (float)N, W);
+#define CAP_SMOOTH(RM)                                                                        \
+  hipLaunchKernelGGL(smooth_kernel<RM>, grid, dim3(kSmoothThreads), 0, as_stream(stream),     \
+                     counts_dev, probs_dev, (int)ny, (int)nx, (int)radius, (float)N, W)
+  switch (smooth_bucket(radius)) {
+    case 2: CAP_SMOOTH(2); break;
+    case 3: CAP_SMOOTH(3); break;
+    case 4: CAP_SMOOTH(4); break;
+    case 8: CAP_SMOOTH(8); break;
+    default: CAP_SMOOTH(16); break;
+  }
+#undef CAP_SMOOTH
   CAP_HIP(hipGetLastError());
   return CAP_OK;
 }
