@@ -4,22 +4,28 @@
 // prediction grids, and the exponentially weighted update of the reference
 // controls.
 //
-// Layout on gfx950: one lane per sample for the rollout (perturbations laid
-// out [T][N][2] so that a wavefront reads 64 consecutive (a, omega) pairs per
-// step; the reference control of step t is uniform and comes through scalar
-// loads).  The robot state and the cost run in FP64: the collision term is a
-// step function of the grid cell, and FP64 positions keep the cell decisions
-// of this kernel and of an FP64 reference identical except within ~1e-12 m of
-// a cell edge.  The update runs one block per step t; every block recomputes
-// min S and the weight sum with the same fixed-order reduction, so the result
-// does not depend on the launch.
+// Layout on gfx950: one sample per lane, 64 samples per block, and the steps of
+// a chunk dealt to the block's waves.  A sample's trajectory is serial only in
+// its four running sums (v, theta, then x, y: one add a step each); the work of
+// a step -- FP64 sine and cosine, the grid read, the cost -- needs no other
+// step's.  So the waves stage the controls, two waves run the sums of v and
+// theta through LDS, all waves take their steps' sine and cosine, two waves run
+// x and y, and all waves add their steps' costs (perturbations laid out
+// [T][N][2]: a wave reads 64 consecutive (a, omega) pairs per step).  The robot
+// state and the cost run in FP64: the collision term is a step function of the
+// grid cell, and FP64 positions (every product and sum rounded on its own)
+// keep the cell decisions of this kernel and of an FP64 reference identical
+// except within ~1e-12 m of a cell edge.  The update runs one block per step
+// t; every block recomputes min S and the weight sum with the same fixed-order
+// reduction, so the result does not depend on the launch.
 #include <algorithm>
 
 #include "common.hpp"
 
 namespace capred {
 
-constexpr int kMppiThreads = 256;
+constexpr int kChunkSteps = 48;        // steps of a chunk (3 per wave at 16 waves)
+constexpr int kUpdateThreads = 1024;
 
 struct MppiArgs {
   double z0[4], goal[4];
@@ -33,89 +39,181 @@ struct MppiArgs {
   double* S;            // [N]
 };
 
-__global__ void __launch_bounds__(kMppiThreads) mppi_rollout_kernel(const MppiArgs a) {
-  // every product and sum rounded on its own, like a plain FP64 reference
+// One lane per sample, serial over T: 33 us at 8192 samples x 40 steps (128
+// waves on 1024 SIMDs, each step's sine and cosine on the critical path).
+// W waves share a chunk's steps instead: 10.6 us.
+template <int W>
+__global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) {
 #pragma clang fp contract(off)
-  const int i = blockIdx.x * kMppiThreads + threadIdx.x;
-  if (i >= a.N) return;
-  double x = a.z0[0], y = a.z0[1], v = a.z0[2], th = a.z0[3];
-  double s = 0.0;
+  constexpr int kOwn = kChunkSteps / W;   // steps of a wave per chunk
+  static_assert(kChunkSteps % W == 0 && W >= 2, "a chunk is whole steps per wave");
+  // row t + 1 belongs to step t of the chunk, row 0 to the state before it
+  __shared__ double A[kChunkSteps + 1][64], B[kChunkSteps + 1][64];
+  __shared__ double part[W][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
+  const int is = min(i, a.N - 1);   // lanes past the end repeat the last sample
   const double2* dl = reinterpret_cast<const double2*>(a.delta);
   const size_t plane = (size_t)a.nx * a.ny;
-  for (int t = 1; t <= a.T; ++t) {
-    const double2 d = dl[(size_t)(t - 1) * a.N + i];
-    const double ua = a.U[2 * (t - 1)] + d.x;
-    const double uw = a.U[2 * (t - 1) + 1] + d.y;
-    const double nxp = x + v * cos(th) * a.dt, nyp = y + v * sin(th) * a.dt;
-    v = v + ua * a.dt;
-    th = th + uw * a.dt;
-    x = nxp;
-    y = nyp;
-    const double e0 = x - a.goal[0], e1 = y - a.goal[1], e2 = v - a.goal[2], e3 = th - a.goal[3];
-    if (t < a.T) {
-      s += a.Q[0] * e0 * e0;
-      s += a.Q[1] * e1 * e1;
-      s += a.Q[2] * e2 * e2;
-      s += a.Q[3] * e3 * e3;
-      s += a.R[0] * ua * ua + a.R[1] * uw * uw;
-      if (a.occ && t <= a.H) {
-        const double cx = floor((x - a.x0) / a.cell), cy = floor((y - a.y0) / a.cell);
-        if (cx >= 0.0 && cx < (double)a.nx && cy >= 0.0 && cy < (double)a.ny) {
-          const float p = a.occ[(size_t)(t - 1) * plane + (size_t)cy * a.nx + (size_t)cx];
-          if ((double)p >= a.p_coll) s += a.w_coll;
+  double s = 0.0;
+  double c0 = wave == 0 ? a.z0[2] : a.z0[3];   // wave 0 carries v and x, wave 1 theta and y
+  double c1 = wave == 0 ? a.z0[0] : a.z0[1];
+  for (int t0 = 0; t0 < a.T; t0 += kChunkSteps) {
+    const int tn = min(kChunkSteps, a.T - t0);
+    double ua[kOwn], uw[kOwn], v[kOwn], th[kOwn], x[kOwn], y[kOwn];
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const int t = wave + k * W;
+      if (t < tn) {
+        const double2 d = dl[(size_t)(t0 + t) * a.N + is];
+        ua[k] = a.U[2 * (t0 + t)] + d.x;
+        uw[k] = a.U[2 * (t0 + t) + 1] + d.y;
+        A[t + 1][lane] = ua[k] * a.dt;
+        B[t + 1][lane] = uw[k] * a.dt;
+      }
+    }
+    __syncthreads();
+    if (wave < 2) {
+      double (*R)[64] = wave == 0 ? A : B;
+      R[0][lane] = c0;
+#pragma unroll 8
+      for (int t = 1; t <= tn; ++t) {
+        c0 = c0 + R[t][lane];
+        R[t][lane] = c0;
+      }
+    }
+    __syncthreads();
+    double px[kOwn], py[kOwn];
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const int t = wave + k * W;
+      if (t < tn) {
+        const double vo = A[t][lane], to = B[t][lane];
+        v[k] = A[t + 1][lane];
+        th[k] = B[t + 1][lane];
+        double sn, cs;
+        sincos(to, &sn, &cs);
+        px[k] = vo * cs * a.dt;
+        py[k] = vo * sn * a.dt;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const int t = wave + k * W;
+      if (t < tn) {
+        A[t + 1][lane] = px[k];
+        B[t + 1][lane] = py[k];
+      }
+    }
+    __syncthreads();
+    if (wave < 2) {
+      double (*R)[64] = wave == 0 ? A : B;
+#pragma unroll 8
+      for (int t = 1; t <= tn; ++t) {
+        c1 = c1 + R[t][lane];
+        R[t][lane] = c1;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const int t = wave + k * W;
+      if (t < tn) {
+        x[k] = A[t + 1][lane];
+        y[k] = B[t + 1][lane];
+      }
+    }
+    __syncthreads();   // the next chunk rewrites A and B
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const int t = t0 + wave + k * W + 1;   // 1 .. T
+      if (wave + k * W < tn) {
+        const double e0 = x[k] - a.goal[0], e1 = y[k] - a.goal[1], e2 = v[k] - a.goal[2],
+                     e3 = th[k] - a.goal[3];
+        if (t < a.T) {
+          s += a.Q[0] * e0 * e0;
+          s += a.Q[1] * e1 * e1;
+          s += a.Q[2] * e2 * e2;
+          s += a.Q[3] * e3 * e3;
+          s += a.R[0] * ua[k] * ua[k] + a.R[1] * uw[k] * uw[k];
+          if (a.occ && t <= a.H) {
+            const double cx = floor((x[k] - a.x0) / a.cell), cy = floor((y[k] - a.y0) / a.cell);
+            if (cx >= 0.0 && cx < (double)a.nx && cy >= 0.0 && cy < (double)a.ny) {
+              const float p = a.occ[(size_t)(t - 1) * plane + (size_t)cy * a.nx + (size_t)cx];
+              if ((double)p >= a.p_coll) s += a.w_coll;
+            }
+          }
+          s += a.c_time;
+        } else {
+          s += a.Qf[0] * e0 * e0;
+          s += a.Qf[1] * e1 * e1;
+          s += a.Qf[2] * e2 * e2;
+          s += a.Qf[3] * e3 * e3;
         }
       }
-      s += a.c_time;
-    } else {
-      s += a.Qf[0] * e0 * e0;
-      s += a.Qf[1] * e1 * e1;
-      s += a.Qf[2] * e2 * e2;
-      s += a.Qf[3] * e3 * e3;
     }
   }
-  a.S[i] = s;
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < a.N) {
+    double sum = part[0][lane];
+    for (int w = 1; w < W; ++w) sum += part[w][lane];
+    a.S[i] = sum;
+  }
 }
 
-// Block-wide reduction in a fixed order (per-thread partials, then a tree in LDS).
-template <bool MIN>
-__device__ __forceinline__ double block_fold(double v, double* red) {
-  red[threadIdx.x] = v;
+// Block-wide reduction of M values in a fixed order (a butterfly in each wave,
+// then the waves in order); every thread gets the results.
+template <bool MIN, int M>
+__device__ __forceinline__ void block_fold(double* v, double (*red)[kUpdateThreads / 64]) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      const double x = __shfl_xor(v[k], o, 64);
+      v[k] = MIN ? fmin(v[k], x) : v[k] + x;
+    }
   __syncthreads();
-  for (int o = kMppiThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      red[threadIdx.x] = MIN ? fmin(red[threadIdx.x], red[threadIdx.x + o])
-                             : red[threadIdx.x] + red[threadIdx.x + o];
-    __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < M; ++k) red[k][threadIdx.x >> 6] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    v[k] = red[k][0];
+#pragma unroll
+    for (int w = 1; w < kUpdateThreads / 64; ++w)
+      v[k] = MIN ? fmin(v[k], red[k][w]) : v[k] + red[k][w];
   }
-  const double r = red[0];
-  __syncthreads();
-  return r;
 }
 
 // Block t: U[t] += sum_i w_i delta[t][i] / sum_i w_i, w_i = exp(-(S_i - min S) / tau).
-__global__ void __launch_bounds__(kMppiThreads)
+// Latency-bound (T blocks, each over all N): 1024 threads a block instead of
+// 256 took it from 18 us to 7.1 us at 8192 samples x 40 steps.
+__global__ void __launch_bounds__(kUpdateThreads)
     mppi_update_kernel(const double* __restrict__ S, const double* __restrict__ delta, int N,
                        double tau, double* __restrict__ U) {
-  __shared__ double red[kMppiThreads];
+  __shared__ double red[3][kUpdateThreads / 64];
   const int t = blockIdx.x;
   double m = INFINITY;
-  for (int i = threadIdx.x; i < N; i += kMppiThreads) m = fmin(m, S[i]);
-  const double smin = block_fold<true>(m, red);
-  double den = 0.0, n0 = 0.0, n1 = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < N; i += kUpdateThreads) m = fmin(m, S[i]);
+  block_fold<true, 1>(&m, red);
+  double acc[3] = {0.0, 0.0, 0.0};   // sum w, sum w delta
+  const double rate = 1.0 / tau;
   const double2* dl = reinterpret_cast<const double2*>(delta) + (size_t)t * N;
-  for (int i = threadIdx.x; i < N; i += kMppiThreads) {
-    const double w = exp(-(S[i] - smin) / tau);
+#pragma unroll 8
+  for (int i = threadIdx.x; i < N; i += kUpdateThreads) {
+    const double w = exp((m - S[i]) * rate);
     const double2 d = dl[i];
-    den += w;
-    n0 += w * d.x;
-    n1 += w * d.y;
+    acc[0] += w;
+    acc[1] += w * d.x;
+    acc[2] += w * d.y;
   }
-  den = block_fold<false>(den, red);
-  n0 = block_fold<false>(n0, red);
-  n1 = block_fold<false>(n1, red);
+  block_fold<false, 3>(acc, red);
   if (threadIdx.x == 0) {
-    U[2 * t] += n0 / den;
-    U[2 * t + 1] += n1 / den;
+    U[2 * t] += acc[1] / acc[0];
+    U[2 * t + 1] += acc[2] / acc[0];
   }
 }
 
@@ -173,9 +271,17 @@ extern "C" cap_status cap_mppi_step(const double z0[4], const double goal[4], in
     a.nx = a.ny = 1;
   }
   hipStream_t s = as_stream(stream);
-  hipLaunchKernelGGL(mppi_rollout_kernel, dim3((unsigned)((N + kMppiThreads - 1) / kMppiThreads)),
-                     dim3(kMppiThreads), 0, s, a);
-  hipLaunchKernelGGL(mppi_update_kernel, dim3((unsigned)T), dim3(kMppiThreads), 0, s,
+  // Waves per block by the waves the samples alone bring: 16 (shortest path
+  // through a step chunk) while they fit the chip's 4096 wave slots at four per
+  // SIMD, fewer beyond, where the serial sums of two waves would idle the rest.
+  const unsigned blocks = (unsigned)((N + 63) / 64);
+  if (blocks <= 256)
+    hipLaunchKernelGGL(mppi_rollout_kernel<16>, dim3(blocks), dim3(64 * 16), 0, s, a);
+  else if (blocks <= 1024)
+    hipLaunchKernelGGL(mppi_rollout_kernel<8>, dim3(blocks), dim3(64 * 8), 0, s, a);
+  else
+    hipLaunchKernelGGL(mppi_rollout_kernel<4>, dim3(blocks), dim3(64 * 4), 0, s, a);
+  hipLaunchKernelGGL(mppi_update_kernel, dim3((unsigned)T), dim3(kUpdateThreads), 0, s,
                      (const double*)S_dev, delta_dev, (int)N, cost->tau, U_dev);
   CAP_HIP(hipGetLastError());
   return CAP_OK;
