@@ -259,6 +259,182 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
   for (int m = 0; m < M; ++m) k_out[m] = cdf_index<KT>(C[m], u[m] * acc[m], KT);
 }
 
+// ---------------------------------------------------------------- far draws
+// Most particles are many steps away from their goal, and there the exponents
+// of all K headings follow from a few harmonics of the heading angle.  With
+// r = |a|, x = |s| / r and psi the angle between a and s_k,
+//   (|a + s_k| - |a|) / |s| = (1 - x^2/8) cos psi - (x/4) cos 2 psi
+//                             + (x^2/8) cos 3 psi + const + e,  |e| <= 0.098 x^3
+// (x <= 0.15; the constant cancels in the policy).  Of a particle's features
+// f_m = nb |s| (...) u^m (u the unit vector of a) the exponents of the four
+// headings theta + 90 j are even + odd, -even + odd', even - odd and
+// -even - odd', so that 16 headings take 36 operations instead of the 96 and the
+// 16 square roots and reciprocals of draw_headings.  The VALU does them: FP32
+// matrix instructions do not overlap with it here, and 24 of them per draw (16
+// headings x 6 coefficients) took as long as what they replaced.
+//
+// The result is a filter, not an approximation of the draw: the heading of the
+// inverse CDF is taken only where u lies farther than `tol` (relative to the
+// total) from the CDF boundaries beside it, a bound on the difference of the two
+// computations; otherwise the caller runs draw_headings.  So the headings are
+// draw_headings' in every case, bit for bit.  tol = c0 + |nb s| (c1 + 0.035 x^3):
+//   * draw_headings itself: each exponent within 6.1 2^-23 |nb s| (dot product,
+//     square roots and reciprocal within 1 ulp, products), so with a weight's
+//     relative error w a CDF value errs by at most w/2; exp2 within 1 ulp; K - 1
+//     additions and the threshold's product, 2^-24 each;
+//   * here: features and their sums within 13 2^-24 |nb s|, the cut-off e |nb s|,
+//     the lattice's rounding of the steps (0.71 units, 0.71 |nb|), exp2 and the
+//     same additions.
+// Together K 2.4e-7 + 2e-7 + |nb s| (6e-7 + 0.034 x^3 + 0.25 / |s|); the host
+// takes 1.25 times the rounding terms.  At most 2 (K - 1) tol of the draws fall
+// back: 2e-4 at K = 16 and small |nb s|.
+//
+// Bound by VALU issue as before, with fewer slots: 120 instructions a draw
+// instead of 170 at K = 16 (17 transcendental instead of 49, two slots each), 182
+// instead of 220 a particle-step with everything else.  A lone cycle of the
+// 16-human workload takes 0.99 ms instead of 1.24, one of 64 humans x 2^20
+// particles (K = 32) 125 ms instead of 178 (each at its best launch shape).
+struct FarConst {
+  float d2;       // smallest |a|^2 (lattice units) the filter takes; inf: none
+  float s4;       // -|s| / 4
+  float c0, c1;   // tol = c0 + |nb s| (c1 + 0.035 x^3)
+};
+constexpr float kFarX = 0.12f;       // largest x
+constexpr float kFarCut = 0.035f;
+
+// cos(11.25 i degrees), i = 0..8
+constexpr float kCos32[9] = {1.f,          0.98078528f, 0.92387953f, 0.83146961f, 0.70710678f,
+                             0.55557023f, 0.38268343f, 0.19509032f, 0.f};
+// cos and sin of i * 11.25 degrees, any i >= 0
+constexpr float cos32(int i) {
+  i &= 31;
+  return i <= 8 ? kCos32[i] : i <= 16 ? -kCos32[16 - i] : i <= 24 ? -kCos32[i - 16] : kCos32[32 - i];
+}
+constexpr float sin32(int i) { return cos32(i + 24); }
+
+// Exponents of headings I, I + K/4, I + K/2, I + 3K/4 and of the following
+// base headings.  f3 is half the third feature.
+template <int KT, int I>
+__device__ __forceinline__ void far_exponents(float f1x, float f1y, float f2x, float f2y,
+                                              float f3x, float f3y, float* E) {
+  if constexpr (I < KT / 4) {
+    constexpr int a = I * (32 / KT);   // theta_I in units of 11.25 degrees
+    float o0, o1, e, h;                // exponents +-h e +- o0 (0, 180), +- o1 (90, 270)
+    if constexpr (a == 0) {
+      o0 = fmaf(2.f, f3x, f1x);
+      o1 = fmaf(-2.f, f3y, f1y);
+      e = f2x;
+      h = 1.f;
+    } else if constexpr (a == 4) {
+      const float p = fmaf(-2.f, f3x, f1x), q = fmaf(2.f, f3y, f1y);
+      o0 = p + q;
+      o1 = q - p;
+      e = f2y;
+      h = 1.f;
+    } else if constexpr (a == 2) {
+      const float m = fmaf(2.f, f3y, f1x), n = fmaf(2.f, f3x, f1y);
+      o0 = fmaf(cos32(2), m, sin32(2) * n);
+      o1 = fmaf(cos32(2), n, -(sin32(2) * m));
+      e = f2x + f2y;
+      h = cos32(4);
+    } else if constexpr (a == 6) {
+      const float m = fmaf(-2.f, f3y, f1x), n = fmaf(-2.f, f3x, f1y);
+      o0 = fmaf(cos32(6), m, sin32(6) * n);
+      o1 = fmaf(cos32(6), n, -(sin32(6) * m));
+      e = f2y - f2x;
+      h = cos32(4);
+    } else {
+      constexpr float c3 = 2.f * cos32(3 * a), s3 = 2.f * sin32(3 * a);
+      o0 = fmaf(c3, f3x, fmaf(s3, f3y, fmaf(cos32(a), f1x, sin32(a) * f1y)));
+      o1 = fmaf(s3, f3x, fmaf(-c3, f3y, fmaf(cos32(a), f1y, -(sin32(a) * f1x))));
+      e = fmaf(cos32(2 * a), f2x, sin32(2 * a) * f2y);
+      h = 1.f;
+    }
+    if constexpr (a == 4) {
+      E[I] = fmaf(cos32(4), o0, e);
+      E[I + KT / 4] = fmaf(cos32(4), o1, -e);
+      E[I + KT / 2] = fmaf(-cos32(4), o0, e);
+      E[I + 3 * KT / 4] = fmaf(-cos32(4), o1, -e);
+    } else if constexpr (a == 2 || a == 6) {
+      E[I] = fmaf(h, e, o0);
+      E[I + KT / 4] = fmaf(-h, e, o1);
+      E[I + KT / 2] = fmaf(h, e, -o0);
+      E[I + 3 * KT / 4] = fmaf(-h, e, -o1);
+    } else {
+      E[I] = e + o0;
+      E[I + KT / 4] = o1 - e;
+      E[I + KT / 2] = e - o0;
+      E[I + 3 * KT / 4] = -e - o1;
+    }
+    far_exponents<KT, I + 1>(f1x, f1y, f2x, f2y, f3x, f3y, E);
+  }
+}
+
+// cdf_index for a power-of-two K, with the distance of thr to the nearest
+// boundary (the search passes both neighbours of thr).
+template <int KT>
+__device__ __forceinline__ int cdf_index_margin(const float* C, float thr, float* margin) {
+  constexpr int L = KT == 4 ? 2 : KT == 8 ? 3 : KT == 16 ? 4 : 5;
+  bool b[L];
+  int pos = 0;
+  float md = INFINITY;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    float v[KT / 2];
+#pragma unroll
+    for (int c = 0; c < (1 << l); ++c) v[c] = C[c * (KT >> l) + (KT >> (l + 1)) - 1];
+#pragma unroll
+    for (int st = l - 1; st >= 0; --st)
+#pragma unroll
+      for (int j = 0; j < (1 << st); ++j) v[j] = b[st] ? v[2 * j + 1] : v[2 * j];
+    b[l] = v[0] <= thr;
+    pos += b[l] ? (KT >> (l + 1)) : 0;
+    md = fminf(md, fabsf(v[0] - thr));
+  }
+  *margin = md;
+  return pos;
+}
+
+// Headings of M far particles; true if all of this lane's are certain.  D2 =
+// |a|^2 >= F.d2, nbs = nb |s|.
+template <int KT, int M>
+__device__ __forceinline__ bool far_headings(const float* ax, const float* ay, const float* D2,
+                                             const float* nbs, const float* u, const FarConst& F,
+                                             int* k_out) {
+  static_assert(KT == 8 || KT == 16 || KT == 32, "headings in quarter turns");
+  float C[M][KT], acc[M], tol[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const float ir = __builtin_amdgcn_rsqf(D2[m]);
+    const float x4 = F.s4 * ir, xx = x4 * x4;                      // -x / 4, x^2 / 16
+    const float n1 = nbs[m] * ir * fmaf(xx, -2.f, 1.f);            // nb s (1 - x^2/8) / r
+    tol[m] = fmaf(nbs[m], fmaf(x4 * xx, 64.f * kFarCut, -F.c1), F.c0);   // nbs, x4 <= 0
+    const float xi = x4 * ir;
+    const float wx = ax[m] * xi, wy = ay[m] * xi;                  // -(x/4) u
+    const float f1x = ax[m] * n1, f1y = ay[m] * n1;
+    const float f2x = fmaf(f1x, wx, -(f1y * wy)), f2y = fmaf(f1x, wy, f1y * wx);
+    const float f3x = fmaf(f2x, wx, -(f2y * wy)), f3y = fmaf(f2x, wy, f2y * wx);
+    far_exponents<KT, 0>(f1x, f1y, f2x, f2y, f3x, f3y, C[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < M; ++m) acc[m] = C[m][0] = fast_exp2(C[m][0]);
+#pragma unroll
+  for (int k = 1; k < KT; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      acc[m] += fast_exp2(C[m][k]);
+      C[m][k] = acc[m];
+    }
+  bool sure = true;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    float margin;
+    k_out[m] = cdf_index_margin<KT>(C[m], u[m] * acc[m], &margin);
+    sure = sure && margin > tol[m] * acc[m];
+  }
+  return sure;
+}
+
 template <int KT, bool SHIFT>
 __device__ __forceinline__ int draw_heading(float ax, float ay, float ib, float u,
                                             const HeadingTable& T, int Krt) {

@@ -122,6 +122,19 @@ inline BeliefModel make_belief_model(const Controls& c, double dt, int B, const 
   return bm;
 }
 
+// The far filter's constants (see FarConst) for steps of `s` lattice units; off
+// (d2 = inf) where K has no filter or the lattice rounds the steps coarsely.
+inline FarConst make_far_const(int K, double s) {
+  FarConst F{INFINITY, 0.f, 0.f, 0.f};
+  if ((K != 8 && K != 16 && K != 32) || s < 4096.0) return F;
+  const double x = kFarX;
+  F.d2 = (float)(s * s / (x * x));
+  F.s4 = (float)(-0.25 * s);
+  F.c0 = (float)(1.25 * (2.4e-7 * K + 2e-7));
+  F.c1 = (float)(1.25 * 6e-7 + 0.25 / s);
+  return F;
+}
+
 // Rollout descriptor of one human.  The start position arrives in metres
 // (host) or is filled in later on the device (batched plans); goals and the
 // step table are rounded to the lattice here, in FP64.
@@ -179,6 +192,7 @@ inline cap_status make_rollout_desc(const Controls& c, double dt, int B, const f
       if (d.T.fx[b] != -d.T.fx[a] || d.T.fy[b] != -d.T.fy[a]) d.sym = 0;
     }
   (void)U;
+  d.far = make_far_const(c.S == 1 ? K : 0, c.v[0] * dt / q);
   // reach check: start +- H steps must stay within int32 (checked again per start)
   const double reach = (double)H * (double)std::max(rx, ry);
   if (reach + (double)grid.nx * kLatticeScale > 2.0e9 || reach + (double)grid.ny * kLatticeScale > 2.0e9)

@@ -21,6 +21,7 @@ struct RolloutDesc {
   int32_t shift;            // 1: subtract the largest exponent (large beta * step)
   int32_t sym;              // 1: S_{k+K/2} = -S_k for every k < K/2 (K even)
   HeadingTable T;           // lattice-unit steps (exact integers) and squared lengths (FP32)
+  FarConst far;             // the filter of far particles' draws (one speed)
   float ibeta[CAP_MAX_B];   // 1 / (-beta q log2(e)), q = lattice pitch
   int32_t GX[CAP_MAX_G], GY[CAP_MAX_G];
   const double* belief;     // [G][B]
@@ -31,7 +32,7 @@ struct RolloutDesc {
 };
 
 struct TileShared {
-  double P[CAP_MAX_J];      // pair CDF (sequential FP64 prefix sums)
+  double P[CAP_MAX_J];      // pair CDF (sequential FP64 prefix sums), then the sort's counts
   int2 S[CAP_MAX_K];        // lattice steps for the dynamic heading index (one speed)
   int2 goal[CAP_MAX_G];
   float ibeta[CAP_MAX_B];
@@ -50,17 +51,17 @@ struct Window {
 };
 
 // Reach window of step t for a start (X0, Y0) on the lattice.
-__device__ __forceinline__ Window step_window_at(const RolloutDesc& d, int32_t X0, int32_t Y0,
-                                                 int t) {
+__device__ __forceinline__ Window step_window_of(int32_t X0, int32_t Y0, int32_t Rx, int32_t Ry,
+                                                 int nx, int ny, int t) {
   // 64-bit only for the reach t * R (up to 2^36); the shifted bounds fit 32 bits,
   // so the clamps stay in scalar 32-bit arithmetic
-  const int64_t rx = (int64_t)t * d.Rx, ry = (int64_t)t * d.Ry;
+  const int64_t rx = (int64_t)t * Rx, ry = (int64_t)t * Ry;
   int lx = (int)floor_shift16((int64_t)X0 - rx), hx = (int)floor_shift16((int64_t)X0 + rx);
   int ly = (int)floor_shift16((int64_t)Y0 - ry), hy = (int)floor_shift16((int64_t)Y0 + ry);
   lx = max(lx, 0);
   ly = max(ly, 0);
-  hx = min(hx, d.nx - 1);
-  hy = min(hy, d.ny - 1);
+  hx = min(hx, nx - 1);
+  hy = min(hy, ny - 1);
   Window win;
   win.x0 = lx;
   win.y0 = ly;
@@ -69,8 +70,9 @@ __device__ __forceinline__ Window step_window_at(const RolloutDesc& d, int32_t X
   return win;
 }
 
-__device__ __forceinline__ Window step_window(const RolloutDesc& d, int t) {
-  return step_window_at(d, d.X0, d.Y0, t);
+__device__ __forceinline__ Window step_window_at(const RolloutDesc& d, int32_t X0, int32_t Y0,
+                                                 int t) {
+  return step_window_of(X0, Y0, d.Rx, d.Ry, d.nx, d.ny, t);
 }
 
 __device__ __forceinline__ uint32_t pick_word(const uint4& w, int s) {
@@ -84,6 +86,64 @@ __device__ __forceinline__ uint32_t pick_word(const uint4& w, int s) {
 // both buffers as one and the first list.
 __host__ __device__ constexpr size_t window_lds_bytes(int cap, int particles_per_tile) {
   return (size_t)2 * cap * sizeof(uint32_t) + (size_t)2 * particles_per_tile * sizeof(uint16_t);
+}
+
+// Deals a tile's particles to the lanes in the order of their (goal, beta)
+// pairs (a counting sort in LDS; each wave takes P * 64 neighbours of the sorted
+// order).  Results do not depend on which lane holds a particle, but the draws'
+// far filter works on whole waves: sorted, the few particles that have reached
+// their goal (or draw sharply) sit together instead of sending every wave the
+// long way.  From kSortSteps steps on, where the sort's barriers are paid for.
+// hist: CAP_MAX_J + 1 words of LDS; the lists: P * blockDim.x entries each.
+constexpr int kSortSteps = 24;
+
+template <int P>
+__device__ __forceinline__ void sort_by_pair(int64_t first, int tile_n, int J, uint32_t* hist,
+                                             uint16_t* lists, uint32_t* idx, int* pair,
+                                             bool* act) {
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+  __syncthreads();   // hist may lie where the pair CDF was read
+  for (int j = tid; j <= J; j += nthr) hist[j] = 0u;
+  __syncthreads();
+  uint32_t rank[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p)   // lanes without a particle sort last, as pair J
+    rank[p] = atomicAdd(hist + (act[p] ? pair[p] : J), 1u);
+  __syncthreads();
+  if (tid < 64) {   // exclusive prefix of the J + 1 counts, a run of bins per lane
+    const int per = (J + 64) / 64, j0 = min(lane * per, J + 1), j1 = min(j0 + per, J + 1);
+    uint32_t n = 0;
+    for (int j = j0; j < j1; ++j) n += hist[j];
+    uint32_t before = n;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t v = __shfl_up(before, o, 64);
+      if (lane >= o) before += v;
+    }
+    before -= n;
+    for (int j = j0; j < j1; ++j) {
+      const uint32_t c = hist[j];
+      hist[j] = before;
+      before += c;
+    }
+  }
+  __syncthreads();
+  uint16_t* who = lists;
+  uint16_t* what = lists + P * nthr;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t at = hist[act[p] ? pair[p] : J] + rank[p];
+    who[at] = (uint16_t)(p * nthr + tid);
+    what[at] = (uint16_t)pair[p];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int at = ((tid >> 6) * P + p) * 64 + lane;
+    idx[p] = (uint32_t)first + who[at];
+    pair[p] = what[at];
+    act[p] = at < tile_n;
+  }
+  __syncthreads();   // the lists are the steps' from here on
 }
 
 // Processes particles [first, first + P * blockDim.x) of human d (clipped to N).
@@ -112,20 +172,9 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   const int nthr = blockDim.x;
   const int J = d.G * d.B;
   // ---- shared tables
-  if (tid == 0) {
-    double acc = 0.0;
-    int last = 0;
-    for (int j = 0; j < J; ++j) {
-      const double b = as_global(d.belief)[j];
-      acc += b;
-      sh.P[j] = acc;
-      if (b > 0.0) last = j;
-    }
-    sh.last_pos = last;
-    sh.off[0] = 0u;
-    sh.off[1] = 0u;
-    sh.ntouch[0] = sh.ntouch[1] = sh.ntouch[2] = 0u;
-  }
+  // pair CDF: FP64 prefix sums in pair order, one thread; the other threads
+  // bring the terms into LDS first, so that it does not wait for memory
+  for (int j = tid; j < J; j += nthr) sh.P[j] = as_global(d.belief)[j];
   if constexpr (MS) {
     for (int u = tid; u < d.K * d.S; u += nthr)
       ctl[u] = make_float4(d.T.fx[u], d.T.fy[u], d.T.s2[u], 0.f);
@@ -135,24 +184,38 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   for (int g = tid; g < d.G; g += nthr) sh.goal[g] = make_int2(d.GX[g], d.GY[g]);
   for (int b = tid; b < d.B; b += nthr) sh.ibeta[b] = d.ibeta[b];
   __syncthreads();
+  if (tid == 0) {
+    double acc = 0.0;
+    int last = 0;
+#pragma unroll 8
+    for (int j = 0; j < J; ++j) {
+      const double b = sh.P[j];
+      acc += b;
+      sh.P[j] = acc;
+      if (b > 0.0) last = j;
+    }
+    sh.last_pos = last;
+    sh.off[0] = 0u;
+    sh.off[1] = 0u;
+    sh.ntouch[0] = sh.ntouch[1] = sh.ntouch[2] = 0u;
+  }
+  __syncthreads();
 
   // ---- per-particle (beta, g) draw, held for the whole horizon
+  constexpr bool kFar = !SHIFT && !MS && (KT == 8 || KT == 16 || KT == 32);
   const uint32_t c3_pair = 2u * d.cycle, c3_head = 2u * d.cycle + 1u;
-  int64_t idx[P];
+  const int tile_n = (int)min((int64_t)P * nthr, (int64_t)d.N - first);   // particles of the tile
+  uint32_t idx[P];
+  int pair[P];
   bool act[P];
-  int32_t X[P], Y[P], GXp[P], GYp[P];
-  float ib[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    idx[p] = first + (int64_t)p * nthr + tid;
-    act[p] = idx[p] < d.N;
-    X[p] = d.X0;
-    Y[p] = d.Y0;
-    GXp[p] = 0;
-    GYp[p] = 0;
-    ib[p] = 1.f;
+    const int local = p * nthr + tid;
+    idx[p] = (uint32_t)first + (uint32_t)local;
+    act[p] = local < tile_n;
+    pair[p] = 0;
     if (act[p]) {
-      const uint4 w = philox10((uint32_t)idx[p], 0u, d.human, c3_pair, seed_lo, seed_hi);
+      const uint4 w = philox10(idx[p], 0u, d.human, c3_pair, seed_lo, seed_hi);
       const double u = uniform24d(w.x);
       int lo = 0, hi = J;
       while (lo < hi) {
@@ -160,21 +223,46 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
         if (sh.P[mid] > u) hi = mid;
         else lo = mid + 1;
       }
-      const int j = lo < J ? lo : sh.last_pos;
-      const int g = j / d.B, b = j - g * d.B;
+      pair[p] = lo < J ? lo : sh.last_pos;
+      if (d.trace_pair) as_global(d.trace_pair)[idx[p]] = pair[p];
+    }
+  }
+  uint16_t* lists = reinterpret_cast<uint16_t*>(win + 2 * cap);
+  if (kFar && d.H >= kSortSteps)
+    sort_by_pair<P>(first, tile_n, J, reinterpret_cast<uint32_t*>(sh.P), lists, idx, pair, act);
+  int32_t X[P], Y[P], GXp[P], GYp[P];
+  float ib[P], nbs[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    X[p] = d.X0;
+    Y[p] = d.Y0;
+    // lanes past the last particle: far from a goal, every heading alike
+    GXp[p] = (int32_t)((uint32_t)d.X0 - (1u << 28));
+    GYp[p] = d.Y0;
+    ib[p] = 1.f;
+    nbs[p] = 0.f;
+    if (act[p]) {
+      const int g = pair[p] / d.B, b = pair[p] - g * d.B;
       GXp[p] = sh.goal[g].x;
       GYp[p] = sh.goal[g].y;
       ib[p] = sh.ibeta[b];
-      if (d.trace_pair) as_global(d.trace_pair)[idx[p]] = j;
+      nbs[p] = -4.f * d.far.s4 / ib[p];
     }
   }
 
-  const size_t plane = (size_t)d.nx * (size_t)d.ny;
+  // The descriptor's fields that every step reads, in scalar registers for the
+  // whole tile: it lies in memory that the loop's stores could alias, so each
+  // use would be a load and a wait.
+  const int H = d.H, nx = d.nx, ny = d.ny, X0 = d.X0, Y0 = d.Y0, Rx = d.Rx, Ry = d.Ry;
+  const uint32_t human = d.human;
+  uint32_t* const counts = d.counts;
+  uint8_t* const trace_k = d.trace_k;
+  const FarConst fc = d.far;
+  const size_t plane = (size_t)nx * (size_t)ny;
   uint4 rw[P];
   const int list_cap = P * nthr;
-  uint16_t* lists = reinterpret_cast<uint16_t*>(win + 2 * cap);
   int m3 = 1;  // t mod 3
-  for (int t = 1; t <= d.H; ++t, m3 = (m3 == 2 ? 0 : m3 + 1)) {
+  for (int t = 1; t <= H; ++t, m3 = (m3 == 2 ? 0 : m3 + 1)) {
     const int s = (t - 1) & 3;
     if (s == 0) {
       // The round keys (key + r * Weyl constant) are derived from the seed here,
@@ -185,9 +273,9 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
       asm volatile("" : "+s"(klo), "+s"(khi));
 #pragma unroll
       for (int p = 0; p < P; ++p)
-        rw[p] = philox10((uint32_t)idx[p], (uint32_t)((t - 1) >> 2), d.human, c3_head, klo, khi);
+        rw[p] = philox10(idx[p], (uint32_t)((t - 1) >> 2), human, c3_head, klo, khi);
     }
-    const Window wd = step_window(d, t);
+    const Window wd = step_window_of(X0, Y0, Rx, Ry, nx, ny, t);
     // two 16-bit counters per LDS word (a tile never holds 65536 particles);
     // rows padded to an even number of cells
     const int half_w = (wd.w + 1) >> 1;
@@ -198,61 +286,69 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
     uint16_t* list = single ? lists : lists + (t & 1) * list_cap;
     // both buffers: the previous step's flush (of either buffer) must be over
     if (single) __syncthreads();
-    uint32_t* grid_t = d.counts + (size_t)(t - 1) * plane;
-    bool off_any = false;
+    uint32_t* grid_t = counts + (size_t)(t - 1) * plane;
     // Draws of all P particles first, then their emplacement: the draws are
     // independent dependency chains (transcendental latency), which the
     // scheduler can interleave only while no branch separates them.  Each
     // particle's step word is rw[p].x; the remaining words move down, so the
     // word is picked without branching on the step's phase.
     int kk[P];
-    if constexpr (PAIR) {
-      static_assert(P % 2 == 0 && !MS, "paired draws need an even P and one speed");
+    if constexpr (MS) {
 #pragma unroll
-      for (int p = 0; p < P; p += 2) {
-        float ax[2], ay[2], ibm[2], um[2];
-        int ko[2];
+      for (int p = 0; p < P; ++p) {
+        const float u = uniform24f(rw[p].x);
+        rw[p] = make_uint4(rw[p].y, rw[p].z, rw[p].w, 0u);
+        const int k = draw_control<KT, SHIFT>((float)(X[p] - GXp[p]), (float)(Y[p] - GYp[p]),
+                                              ib[p], u, d.T, d.S, d.smask, d.s_last, ctl);
+        const float4 c = ctl[k];
+        X[p] += (int32_t)c.x;
+        Y[p] += (int32_t)c.y;
+        kk[p] = k;
+      }
+    } else {
+      // computed for inactive lanes too (harmless state), so that the draws
+      // stay in few basic blocks; only emplacement is predicated
+      constexpr int M = PAIR ? 2 : 1;
+      static_assert(P % M == 0, "paired draws need an even P");
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
+      for (int p = 0; p < P; p += M) {
+        float ax[M], ay[M], ibm[M], um[M];
+        int ko[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
           ax[m] = (float)(X[p + m] - GXp[p + m]);
           ay[m] = (float)(Y[p + m] - GYp[p + m]);
           ibm[m] = ib[p + m];
           um[m] = uniform24f(rw[p + m].x);
           rw[p + m] = make_uint4(rw[p + m].y, rw[p + m].z, rw[p + m].w, 0u);
         }
-        draw_headings<KT, SHIFT, 2>(ax, ay, ibm, um, d.T, ko);
+        bool sure = false;   // uniform in the wave
+        if constexpr (kFar) {
+          float D2[M];
+          bool far = true;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
+          for (int m = 0; m < M; ++m) {
+            D2[m] = fmaf(ax[m], ax[m], ay[m] * ay[m]);
+            far = far && D2[m] >= fc.d2;
+          }
+          if (__all(far))
+            sure = __all(far_headings<KT, M>(ax, ay, D2, nbs + p, um, fc, ko));
+        }
+        if (!sure) {
+          // keeps the table's loads (48 scalars at K = 16) out of the common path
+          if constexpr (kFar) asm volatile("" ::: "memory");
+          if constexpr (PAIR)
+            draw_headings<KT, SHIFT, 2>(ax, ay, ibm, um, d.T, ko);
+          else
+            ko[0] = draw_heading<KT, SHIFT>(ax[0], ay[0], ibm[0], um[0], d.T, d.K);
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
           const int2 st = sh.S[ko[m]];
           X[p + m] += st.x;
           Y[p + m] += st.y;
           kk[p + m] = ko[m];
         }
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        // computed for inactive lanes too (harmless state), so that the P
-        // particles stay in one basic block; only emplacement is predicated
-        const float u = uniform24f(rw[p].x);
-        rw[p] = make_uint4(rw[p].y, rw[p].z, rw[p].w, 0u);
-        int k;
-        if constexpr (MS)
-          k = draw_control<KT, SHIFT>((float)(X[p] - GXp[p]), (float)(Y[p] - GYp[p]), ib[p], u,
-                                      d.T, d.S, d.smask, d.s_last, ctl);
-        else
-          k = draw_heading<KT, SHIFT>((float)(X[p] - GXp[p]), (float)(Y[p] - GYp[p]), ib[p], u,
-                                      d.T, d.K);
-        if constexpr (MS) {
-          const float4 c = ctl[k];
-          X[p] += (int32_t)c.x;
-          Y[p] += (int32_t)c.y;
-        } else {
-          const int2 st = sh.S[k];
-          X[p] += st.x;
-          Y[p] += st.y;
-        }
-        kk[p] = k;
       }
     }
     // The draws' results are fixed here (an empty asm that reads and writes
@@ -260,39 +356,60 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
     // emplacement of its particle below.
 #pragma unroll
     for (int p = 0; p < P; ++p) asm volatile("" : "+v"(X[p]), "+v"(Y[p]), "+v"(kk[p]));
+    if (trace_k) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      bool off = false;
-      const int k = kk[p];
-      bool fresh = false;     // this lane turned an empty window word non-empty
-      uint32_t widx = 0;
-      if (act[p]) {
-        if (d.trace_k) as_global(d.trace_k)[(size_t)idx[p] * d.H + (t - 1)] = (uint8_t)k;
-        const int cx = X[p] >> kLatticeShift, cy = Y[p] >> kLatticeShift;
-        if (lds_mode) {
-          // the particle's cell lies in the unclipped reach window, so it is on
-          // the grid exactly when it lies in the clipped window
-          const unsigned lx = (unsigned)(cx - wd.x0), ly = (unsigned)(cy - wd.y0);
-          if (lx < (unsigned)wd.w && ly < (unsigned)wd.h) {
-            widx = __umul24(ly, (unsigned)half_w) + (lx >> 1);  // both below 2^24
-            fresh = atomicAdd(buf + widx, 1u << ((lx & 1u) << 4)) == 0u;
-          } else {
-            off = true;
-          }
-        } else if ((unsigned)cx < (unsigned)d.nx && (unsigned)cy < (unsigned)d.ny) {
-          global_add(grid_t + (size_t)cy * d.nx + cx, 1u);
-        } else {
-          off = true;
+      for (int p = 0; p < P; ++p)
+        if (act[p]) as_global(trace_k)[(size_t)idx[p] * H + (t - 1)] = (uint8_t)kk[p];
+    }
+    uint32_t off = 0;   // off-grid particles of the wave
+    if (lds_mode) {
+      // The P adds go out before any result is waited for, and the wave appends
+      // the words that its adds turned non-empty with one addition to the
+      // list's length, so that a step has two LDS round trips instead of 2 P.
+      // The particle's cell lies in the unclipped reach window, so it is on the
+      // grid exactly when it lies in the clipped window.
+      uint32_t widx[P], old[P];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const unsigned lx = (unsigned)((X[p] >> kLatticeShift) - wd.x0),
+                       ly = (unsigned)((Y[p] >> kLatticeShift) - wd.y0);
+        const bool in = act[p] && lx < (unsigned)wd.w && ly < (unsigned)wd.h;
+        widx[p] = __umul24(ly, (unsigned)half_w) + (lx >> 1);  // both below 2^24
+        old[p] = 1u;
+        if (in) old[p] = atomicAdd(buf + widx[p], 1u << ((lx & 1u) << 4));
+        off += __popcll(__ballot(act[p] && !in));
+      }
+#pragma unroll
+      for (int p = 0; p < P; ++p) asm volatile("" : "+v"(old[p]));
+      uint64_t fresh[P];
+      uint32_t n_fresh = 0;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        fresh[p] = __ballot(old[p] == 0u);
+        n_fresh += __popcll(fresh[p]);
+      }
+      if (n_fresh) {
+        uint32_t at = 0;
+        if ((tid & 63) == 0) at = atomicAdd(&sh.ntouch[m3], n_fresh);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(fresh[p] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)fresh[p], 0u));
+          if (old[p] == 0u) list[at + below] = (uint16_t)widx[p];
+          at += __popcll(fresh[p]);
         }
       }
-      // append of the freshly touched words and the off-grid count: the
-      // compiler's atomic optimizer turns each uniform-address increment into
-      // one LDS atomic per wavefront plus a lane prefix count
-      if (fresh) list[atomicAdd(&sh.ntouch[m3], 1u)] = (uint16_t)widx;
-      off_any |= off;
-      if (off) atomicAdd(&sh.off[t & 1], 1u);
+    } else {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int cx = X[p] >> kLatticeShift, cy = Y[p] >> kLatticeShift;
+        const bool in = act[p] && (unsigned)cx < (unsigned)nx && (unsigned)cy < (unsigned)ny;
+        if (in) global_add(grid_t + (size_t)cy * nx + cx, 1u);
+        off += __popcll(__ballot(act[p] && !in));
+      }
     }
-    (void)off_any;
+    if (off && (tid & 63) == 0) atomicAdd(&sh.off[t & 1], off);
     __syncthreads();
     // ---- flush the touched words of step t's window, clear them
     if (lds_mode) {
@@ -303,8 +420,8 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
       // 2^-22 (w + 1/2) / half_w <= 2^-22 * 65536 / half_w, since w < 2^16.
       const float rhw = fast_rcp((float)half_w), hrhw = 0.5f * rhw;
       // byte offset of the window's first cell within the step's plane (< 2^30)
-      const uint32_t base4 = 4u * ((uint32_t)wd.y0 * (uint32_t)d.nx + (uint32_t)wd.x0);
-      const uint32_t nx4 = 4u * (uint32_t)d.nx;
+      const uint32_t base4 = 4u * ((uint32_t)wd.y0 * (uint32_t)nx + (uint32_t)wd.x0);
+      const uint32_t nx4 = 4u * (uint32_t)nx;
       char* gbase = reinterpret_cast<char*>(grid_t);
       const uint32_t nt = sh.ntouch[m3];
       for (uint32_t i = tid; i < nt; i += nthr) {
