@@ -6,14 +6,13 @@
 
 namespace capred {
 
-// LDS budget of the histogram windows of the single-human kernel (two
-// buffers: the step being binned and the step being flushed).
-constexpr int kPlainThreads = 256;
-constexpr int kPlainLdsBytes = 40 * 1024;
-
-__global__ void __launch_bounds__(256) zero_u32_kernel(uint32_t* __restrict__ p, size_t n) {
+// Clears the n counts and the m off-grid counters (nullable).
+__global__ void __launch_bounds__(256)
+    zero_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t* __restrict__ q, size_t m) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q)
+    for (size_t v = i; v < m; v += stride) q[v] = 0u;
   const size_t head = (reinterpret_cast<uintptr_t>(p) & 15u) ? 0 : n / 4;
   uint4* p4 = reinterpret_cast<uint4*>(p);
   for (size_t v = i; v < head; v += stride) p4[v] = make_uint4(0u, 0u, 0u, 0u);
@@ -38,7 +37,7 @@ __global__ void __launch_bounds__(256) normalize_kernel(const uint32_t* __restri
 }
 
 template <int KT, int P, bool SHIFT, bool MS>
-__global__ void __launch_bounds__(kPlainThreads)
+__global__ void __launch_bounds__(1024)
     rollout_plain_kernel(const RolloutDesc d, uint32_t seed_lo, uint32_t seed_hi, int cap) {
   __shared__ TileShared sh;
   __shared__ float4 ctl[MS ? CAP_MAX_U : 1];
@@ -111,48 +110,87 @@ __global__ void __launch_bounds__(256)
   if (i < n) out[i] = philox10(c0 + (uint32_t)i, c1, c2, c3, slo, shi);
 }
 
-cap_status launch_zero(uint32_t* p, size_t n, hipStream_t s) {
-  if (n == 0) return CAP_OK;
+static cap_status launch_zero(uint32_t* p, size_t n, uint32_t* q, size_t m, hipStream_t s) {
   const size_t blocks = std::min<size_t>((n / 4 + 255) / 256 + 1, 4096);
-  hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, n);
+  hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, n, q, m);
   CAP_HIP(hipGetLastError());
   return CAP_OK;
+}
+
+// Words of one window buffer for blocks of `threads`: what the widest step
+// window needs, at most the share of a CU's LDS that leaves the other blocks of
+// that size their place (a 1024-thread block is alone on its CU at 128
+// registers).  A window of up to twice the buffer still fits (see
+// rollout_tile_body).
+static int plain_window_words(const RolloutDesc& d, int threads) {
+  const int most = (threads <= 256 ? 40 : threads <= 512 ? 64 : 128) * 1024 / (2 * (int)sizeof(uint32_t));
+  int need = 0;
+  for (int t = d.H; t >= 1 && need < most; --t) {
+    const int64_t rx = (int64_t)t * d.Rx, ry = (int64_t)t * d.Ry;
+    const int64_t x0 = std::max<int64_t>((d.X0 - rx) >> kLatticeShift, 0),
+                  x1 = std::min<int64_t>((d.X0 + rx) >> kLatticeShift, d.nx - 1),
+                  y0 = std::max<int64_t>((d.Y0 - ry) >> kLatticeShift, 0),
+                  y1 = std::min<int64_t>((d.Y0 + ry) >> kLatticeShift, d.ny - 1);
+    if (x1 < x0 || y1 < y0) continue;
+    need = (int)std::max<int64_t>(need, std::min<int64_t>((x1 - x0 + 2) / 2 * (y1 - y0 + 1), most));
+  }
+  return std::max(64, (need + 3) & ~3);
 }
 
 template <int KT, int P, bool MS>
-static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t shi, int cap,
+static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t shi, int threads,
                                  hipStream_t s) {
-  const int64_t per_block = (int64_t)P * kPlainThreads;
+  const int64_t per_block = (int64_t)P * threads;
   const int64_t blocks = (d.N + per_block - 1) / per_block;
-  const size_t lds = window_lds_bytes(cap, P * kPlainThreads);
+  const int cap = plain_window_words(d, threads);
+  const size_t lds = window_lds_bytes(cap, P * threads);
   if (d.shift)
     hipLaunchKernelGGL((rollout_plain_kernel<KT, P, true, MS>), dim3((unsigned)blocks),
-                       dim3(kPlainThreads), lds, s, d, slo, shi, cap);
+                       dim3(threads), lds, s, d, slo, shi, cap);
   else
     hipLaunchKernelGGL((rollout_plain_kernel<KT, P, false, MS>), dim3((unsigned)blocks),
-                       dim3(kPlainThreads), lds, s, d, slo, shi, cap);
+                       dim3(threads), lds, s, d, slo, shi, cap);
   CAP_HIP(hipGetLastError());
   return CAP_OK;
 }
 
+// Shape of the launch.  Few particles are bound by the latency of a step, which
+// a block of one wave keeps shortest, so blocks grow (64 threads at a time)
+// only as far as one block per CU asks.  Many particles are bound by the
+// device-scope atomics of the flush: a tile adds each cell it touched once per
+// step, so larger tiles add less.  2^18 particles x 50 steps (K = 16): 1024
+// blocks of 256 threads issue 4.75e6 atomics and the call takes 337-378 us, with
+// 256 blocks of 1024 threads 214; 8192 particles x 10 steps (96 controls): 32
+// blocks of 256 threads 73.9 us, 128 of 64 threads 69.0.
+template <int KT, bool MS>
+static cap_status launch_plain_k(const RolloutDesc& d, uint32_t slo, uint32_t shi,
+                                 hipStream_t s) {
+  const int64_t cus = std::max(1, cap_device_cu_count());
+  const int64_t waves = (d.N + 64 * cus - 1) / (64 * cus);   // per CU
+  if constexpr (!MS) {
+    if (waves > 32) return launch_plain_t<KT, 4, MS>(d, slo, shi, 1024, s);
+    if (waves > 16) return launch_plain_t<KT, 2, MS>(d, slo, shi, 1024, s);
+  }
+  return launch_plain_t<KT, 1, MS>(d, slo, shi, 64 * (int)std::min<int64_t>(waves, 16), s);
+}
+
 static cap_status launch_plain(const RolloutDesc& d, uint32_t slo, uint32_t shi, hipStream_t s) {
-  const int cap = kPlainLdsBytes / (2 * (int)sizeof(uint32_t));
   // specialised kernels assume a point-symmetric step table; several speeds
   // need one (checked when the descriptor is built)
   if (d.S > 1) {
     switch (d.K) {
-      case 4: return launch_plain_t<4, 1, true>(d, slo, shi, cap, s);
-      case 8: return launch_plain_t<8, 1, true>(d, slo, shi, cap, s);
-      case 16: return launch_plain_t<16, 1, true>(d, slo, shi, cap, s);
-      default: return launch_plain_t<32, 1, true>(d, slo, shi, cap, s);
+      case 4: return launch_plain_k<4, true>(d, slo, shi, s);
+      case 8: return launch_plain_k<8, true>(d, slo, shi, s);
+      case 16: return launch_plain_k<16, true>(d, slo, shi, s);
+      default: return launch_plain_k<32, true>(d, slo, shi, s);
     }
   }
   switch (d.sym ? d.K : 0) {
-    case 4: return launch_plain_t<4, 1, false>(d, slo, shi, cap, s);
-    case 8: return launch_plain_t<8, 1, false>(d, slo, shi, cap, s);
-    case 16: return launch_plain_t<16, 1, false>(d, slo, shi, cap, s);
-    case 32: return launch_plain_t<32, 1, false>(d, slo, shi, cap, s);
-    default: return launch_plain_t<0, 1, false>(d, slo, shi, cap, s);
+    case 4: return launch_plain_k<4, false>(d, slo, shi, s);
+    case 8: return launch_plain_k<8, false>(d, slo, shi, s);
+    case 16: return launch_plain_k<16, false>(d, slo, shi, s);
+    case 32: return launch_plain_k<32, false>(d, slo, shi, s);
+    default: return launch_plain_k<0, false>(d, slo, shi, s);
   }
 }
 
@@ -186,8 +224,9 @@ extern "C" cap_status cap_predict_occupancy(const cap_model* model, const cap_gr
   d.trace_k = trace_k_dev;
   d.trace_pair = trace_pair_dev;
   hipStream_t s = as_stream(stream);
-  if ((st = launch_zero(counts_dev, (size_t)H * grid->nx * grid->ny, s)) != CAP_OK) return st;
-  if (offgrid_dev && (st = launch_zero(offgrid_dev, (size_t)H, s)) != CAP_OK) return st;
+  if ((st = launch_zero(counts_dev, (size_t)H * grid->nx * grid->ny, offgrid_dev, (size_t)H, s)) !=
+      CAP_OK)
+    return st;
   return launch_plain(d, (uint32_t)seed, (uint32_t)(seed >> 32), s);
 }
 
