@@ -105,18 +105,15 @@ __device__ __forceinline__ void policy_terms(const BeliefModel& m, float zx, flo
 // policy_terms for a model of exactly KT controls (KT > 0), for the batched
 // log-likelihood: the loops over the controls are unrolled (the KT distance
 // chains are independent, which the runtime-length loops above hide from the
-// scheduler), the chosen control's Delta is picked by a select in the loop
-// instead of a dynamic index, and the distances take the hardware square root
+// scheduler), the chosen control's Delta is evaluated from its own step by the
+// same operations (st: (sx, sy, s2) per control in LDS), each beta's term goes to
+// out(b, term) at once, and the distances take the hardware square root
 // and reciprocal (within 1 ulp) in place of the IEEE ones: the log-likelihood's
 // error bar is 1e-5 of its magnitude, not the posterior's absolute 1e-5.
-template <int KT>
-__device__ __forceinline__ void policy_terms_fixed(const BeliefModel& m, float zx, float zy,
+template <int KT, class Out>
+__device__ __forceinline__ void policy_terms_fixed(const float4* st, float zx, float zy,
                                                    int ks, float gx, float gy,
-                                                   const float* beta, int B, float* out) {
-  if (ks < 0) {
-    for (int b = 0; b < B; ++b) out[b] = 0.f;
-    return;
-  }
+                                                   const float* beta, int B, Out out) {
   const float ax = zx - gx, bx = ax - zx;
   const float ax_lo = (zx - (ax - bx)) + (-gx - bx);
   const float ay = zy - gy, by = ay - zy;
@@ -124,16 +121,19 @@ __device__ __forceinline__ void policy_terms_fixed(const BeliefModel& m, float z
   const float D2 = fmaf(ax, ax, ay * ay);
   const float D = fast_sqrt(D2);
   const float ax2 = ax + ax, ay2 = ay + ay;
+  auto delta = [&](float4 c) {
+    const float corr = fmaf(2.f * ax_lo, c.x, fmaf(2.f * ay_lo, c.y, c.z));
+    const float n = fmaf(ax2, c.x, fmaf(ay2, c.y, corr));
+    const float d = fast_sqrt(fmaxf(D2 + n, 0.f));
+    return n * fast_rcp(d + D);
+  };
+  const float dks = delta(st[ks]);
   float dl[KT];
-  float dmin = INFINITY, dks = 0.f;
+  float dmin = INFINITY;
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
-    const float corr = fmaf(2.f * ax_lo, m.sx[k], fmaf(2.f * ay_lo, m.sy[k], m.s2[k]));
-    const float n = fmaf(ax2, m.sx[k], fmaf(ay2, m.sy[k], corr));
-    const float d = fast_sqrt(fmaxf(D2 + n, 0.f));
-    dl[k] = n * fast_rcp(d + D);
+    dl[k] = delta(st[k]);
     dmin = fminf(dmin, dl[k]);
-    dks = k == ks ? dl[k] : dks;
   }
   // logits in base 2: a_k = -beta log2(e) Delta_k - c with the shift c = -beta
   // log2(e) min_k Delta_k (rounded), so pi_k = 2^a_k / sum_j 2^a_j for any c
@@ -144,7 +144,7 @@ __device__ __forceinline__ void policy_terms_fixed(const BeliefModel& m, float z
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < KT; ++k) s += fast_exp2(fmaf(nb2, dl[k], -mx2));
-    out[b] = (fmaf(nb2, dks, -mx2) - fast_log2(s)) * kLn2;
+    out(b, (fmaf(nb2, dks, -mx2) - fast_log2(s)) * kLn2);
   }
 }
 

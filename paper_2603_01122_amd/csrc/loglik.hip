@@ -1,11 +1,15 @@
 // loglik.hip -- batched trajectory log-likelihood (product form of
 // Eq. beta_update over each track) and its adjoint with respect to the goal
-// positions and log beta.  A wavefront takes 64 / L goals of one track, and
-// each goal's L lanes stride over the observed steps (L = 64: one goal per
-// wave).  FP32 policy terms are accumulated per lane in FP64 and reduced
-// across each goal's lanes by a fixed butterfly, so for a given L results are
-// bitwise reproducible.  The adjoint writes per-(track, goal) partials to the
-// workspace and a second kernel sums them in a fixed order (no atomics).
+// positions and log beta.  A block takes one track (and, beyond 21 goals, a
+// slice of the goals): the controls of its steps are recovered once into LDS,
+// each lane keeps one goal, and a wave takes chunks of 64 / goals consecutive
+// steps, the block's waves in turn.  So a track leaves idle lanes only in its
+// last chunk, and the waves that have no chunk left end.  Both kernels are bound
+// by the issue of their (beta, heading) terms.  FP32 policy terms are
+// accumulated per lane in FP64 and reduced over lanes and waves in a fixed
+// order, so for a given launch shape results are bitwise reproducible.  The
+// adjoint writes per-track partials to the workspace and a second kernel sums
+// them in a fixed order (no atomics).
 #include <algorithm>
 #include <mutex>
 
@@ -13,35 +17,7 @@
 
 namespace capred {
 
-constexpr int kLLThreads = 256;  // 4 wavefronts
-
-// Sum over the 2^lg lanes of this lane's goal (a butterfly inside the group).
-__device__ __forceinline__ double group_sum(double v, int lg) {
-  for (int o = (1 << lg) >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// This lane's (track, goal, first step) for 2^lg lanes per goal; `on` is false
-// for the lanes of a wave's last goal slots beyond G (they add nothing but
-// take part in the group sums).
-struct LLItem {
-  int n, g, sub;
-  bool on;
-};
-
-__device__ __forceinline__ bool ll_item(int G, int N, int lg, LLItem* it) {
-  const int lane = threadIdx.x & 63;
-  const int gpw = 64 >> lg;                    // goals per wave
-  const int groups = (G + gpw - 1) / gpw;      // waves per track
-  const int wave = blockIdx.x * (kLLThreads / 64) + (threadIdx.x >> 6);
-  if (wave >= N * groups) return false;        // whole wavefront exits together
-  it->n = wave / groups;
-  const int g = (wave - it->n * groups) * gpw + (lane >> lg);
-  it->on = g < G;
-  it->g = it->on ? g : 0;
-  it->sub = lane & ((1 << lg) - 1);
-  return true;
-}
+constexpr int kStepBuf = 1024;    // recovered controls of a block held in LDS
 
 struct LLArgs {
   BeliefModel m;           // K, continuous steps and heading unit vectors
@@ -52,36 +28,88 @@ struct LLArgs {
   const float* log_beta;   // [B] or [N][B]
 };
 
-__device__ __forceinline__ void load_beta(const LLArgs& a, int n, float* beta) {
-  const float* lb = a.per_track ? a.log_beta + (size_t)n * a.B : a.log_beta;
-  for (int b = 0; b < a.B; ++b) beta[b] = expf(lb[b]);
+// A block's share of the work: L lanes per goal, goals [g0, g0 + gn) of a track.
+struct LLShape {
+  int L, slice;   // lanes per goal, goals per slice (L * slice <= 64)
+};
+
+// The step table in LDS, (sx, sy, s2) of a control in one read.  (3 KT scalars do
+// not fit the scalar registers at KT = 32; spilled, each use is a VALU access.)
+__device__ __forceinline__ void load_steps(const BeliefModel& m, float4* st) {
+  for (int k = threadIdx.x; k < m.K; k += blockDim.x)
+    st[k] = make_float4(m.sx[k], m.sy[k], m.s2[k], 0.f);
+}
+
+// Recovers the controls of steps [t0, t0 + n) of a track into ks (255: none).
+__device__ __forceinline__ void recover_steps(const BeliefModel& m, const float* z, int t0, int n,
+                                              uint8_t* ks) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const float* p = z + 2 * (t0 + i);
+    ks[i] = (uint8_t)recover_control(m, p[2] - p[0], p[3] - p[1]);
+  }
+}
+
+// Sum over the L lanes of this lane's goal, complete in its first lane (sub 0).
+__device__ __forceinline__ double goal_sum(double v, int sub, int L) {
+  for (int o = 1; o < L; o <<= 1) {
+    const double x = __shfl_down(v, o, 64);
+    if (sub + o < L) v += x;
+  }
+  return v;
 }
 
 template <int KT>
-__global__ void __launch_bounds__(kLLThreads)
-    loglik_kernel(const LLArgs a, int lg, double* __restrict__ LL) {
-  LLItem it;
-  if (!ll_item(a.G, a.N, lg, &it)) return;
-  const int n = it.n, g = it.g;
-  const int len = it.on ? a.lengths[n] : 0;
+__global__ void __launch_bounds__(1024)
+    loglik_kernel(const LLArgs a, const LLShape sh, double* __restrict__ LL) {
+  __shared__ uint8_t ks[kStepBuf];
+  __shared__ float4 st[CAP_MAX_K];
+  __shared__ float beta[CAP_MAX_B];
+  extern __shared__ double dyn[];    // sums [B][threads], then [waves][goals of the slice][B]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int n = blockIdx.x, g0 = (int)blockIdx.y * sh.slice, gn = min(sh.slice, a.G - g0);
+  const int gl = lane / sh.L, sub = lane - gl * sh.L, B = a.B;
+  const bool on = gl < gn;
+  const int g = g0 + (on ? gl : 0);
+  const int len = a.lengths[n];
   const float* z = a.tracks + (size_t)n * (a.Tmax + 1) * 2;
+  const float* lb = a.per_track ? a.log_beta + (size_t)n * B : a.log_beta;
   const float gx = a.goals[2 * g], gy = a.goals[2 * g + 1];
-  float beta[CAP_MAX_B], terms[CAP_MAX_B];
-  load_beta(a, n, beta);
-  double acc[CAP_MAX_B];
-  for (int b = 0; b < a.B; ++b) acc[b] = 0.0;
-  for (int t = it.sub; t < len; t += 1 << lg) {
-    const float zx = z[2 * t], zy = z[2 * t + 1];
-    const int ks = recover_control(a.m, z[2 * t + 2] - zx, z[2 * t + 3] - zy);
-    if constexpr (KT > 0)
-      policy_terms_fixed<KT>(a.m, zx, zy, ks, gx, gy, beta, a.B, terms);
-    else
-      policy_terms<CAP_MAX_K>(a.m, zx, zy, ks, gx, gy, beta, a.B, terms);
-    for (int b = 0; b < a.B; ++b) acc[b] += (double)terms[b];
+  const int nthr = blockDim.x;
+  double* acc = dyn + threadIdx.x;
+  double* part = dyn + (size_t)B * nthr;
+  for (int b = threadIdx.x; b < B; b += nthr) beta[b] = expf(lb[b]);
+  for (int b = 0; b < B; ++b) acc[b * nthr] = 0.0;
+  load_steps(a.m, st);
+  for (int t0 = 0; t0 < len; t0 += kStepBuf) {
+    const int tn = min(kStepBuf, len - t0);
+    __syncthreads();
+    recover_steps(a.m, z, t0, tn, ks);
+    __syncthreads();
+    for (int i = wave * sh.L + sub; i < tn; i += W * sh.L) {
+      const int k = ks[i];
+      if (!on || k == 255) continue;
+      asm volatile("" ::: "memory");   // the table stays in LDS: held, it takes 3 KT registers
+      const float zx = z[2 * (t0 + i)], zy = z[2 * (t0 + i) + 1];
+      if constexpr (KT > 0) {
+        policy_terms_fixed<KT>(st, zx, zy, k, gx, gy, beta, B,
+                               [&](int b, float v) { acc[b * nthr] += (double)v; });
+      } else {
+        float terms[CAP_MAX_B];
+        policy_terms<CAP_MAX_K>(a.m, zx, zy, k, gx, gy, beta, B, terms);
+        for (int b = 0; b < B; ++b) acc[b * nthr] += (double)terms[b];
+      }
+    }
   }
-  for (int b = 0; b < a.B; ++b) {
-    const double s = group_sum(acc[b], lg);
-    if (it.on && it.sub == 0) LL[((size_t)n * a.B + b) * a.G + g] = s;
+  for (int b = 0; b < B; ++b) {
+    const double s = goal_sum(acc[b * nthr], sub, sh.L);
+    if (on && sub == 0) part[(wave * gn + gl) * B + b] = s;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < gn * B; i += blockDim.x) {
+    double s = part[i];
+    for (int w = 1; w < W; ++w) s += part[w * gn * B + i];
+    const int q = i / B, b = i - q * B;
+    LL[((size_t)n * B + b) * a.G + g0 + q] = s;
   }
 }
 
@@ -90,222 +118,260 @@ __global__ void __launch_bounds__(kLLThreads)
 //   d ell/d log beta = -beta (Delta_{k*} - E_p[Delta]),
 // with yhat_k = (a + s_k)/d_k and, to avoid cancellation between unit vectors,
 //   yhat_k - yhat_* = a (Delta_* - Delta_k)/(d_k d_*) + s_k/d_k - s_*/d_*.
-// KT > 0: the model has KT headings (loops over headings fully unrolled, so
-// the per-heading arrays stay in registers); KT == 0: any K.
+//
+// KT > 0 (the model has KT headings, every loop over them unrolled): Delta is
+// taken relative to its minimum, so the logits need no shift and E[Delta] no
+// subtraction of two like sums.  Per beta the KT probabilities are formed, their
+// sum and first moment, and then added, times w beta / sum, into one coefficient
+// per heading; the unit vectors enter once, after the betas.  That is two FMAs
+// fewer per (beta, heading) than three moments per beta, and leaves three arrays
+// of KT registers live instead of four.  The per-lane sums of d log beta are
+// kept in LDS.  (KT = 32, 1024 tracks x 200 steps x 8 goals x 9 betas: 197 -> 148 us
+// at 128 registers, four waves per SIMD; 152 at 136 registers and three.)
 template <int KT>
-__global__ void __launch_bounds__(kLLThreads)
-    loglik_backward_kernel(const LLArgs a, int lg, const double* __restrict__ dLL,
+__global__ void __launch_bounds__(1024)
+    loglik_backward_kernel(const LLArgs a, const LLShape sh, const double* __restrict__ dLL,
                            double* __restrict__ ws_g, double* __restrict__ ws_b) {
   constexpr int KM = KT > 0 ? KT : CAP_MAX_K;
-  LLItem it;
-  if (!ll_item(a.G, a.N, lg, &it)) return;
-  const int n = it.n, g = it.g;
-  const int len = it.on ? a.lengths[n] : 0;
-  const int K = KT > 0 ? KT : a.m.K, B = a.B;
+  __shared__ uint8_t ks[kStepBuf];
+  __shared__ float4 st[CAP_MAX_K];
+  __shared__ float beta[CAP_MAX_B];
+  __shared__ double red[16][2 * 64];
+  extern __shared__ double dyn[];    // ab [B][threads], then w [B][64] (FP32)
+  const int nthr = blockDim.x, W = nthr >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = blockIdx.x, g0 = (int)blockIdx.y * sh.slice, gn = min(sh.slice, a.G - g0);
+  const int gl = lane / sh.L, sub = lane - gl * sh.L, B = a.B;
+  const bool on = gl < gn;
+  const int g = g0 + (on ? gl : 0);
+  const int K = KT > 0 ? KT : a.m.K;
+  const int len = a.lengths[n];
   const float* z = a.tracks + (size_t)n * (a.Tmax + 1) * 2;
+  const float* lb = a.per_track ? a.log_beta + (size_t)n * B : a.log_beta;
   const float gx = a.goals[2 * g], gy = a.goals[2 * g + 1];
-  float beta[CAP_MAX_B], w[CAP_MAX_B];
-  load_beta(a, n, beta);
-  for (int b = 0; b < B; ++b) w[b] = (float)dLL[((size_t)n * B + b) * a.G + g];
-  double agx = 0.0, agy = 0.0, ab[CAP_MAX_B];
-  for (int b = 0; b < B; ++b) ab[b] = 0.0;
-  float dl[KM], dk[KM];
-  for (int t = it.sub; t < len; t += 1 << lg) {
-    const float zx = z[2 * t], zy = z[2 * t + 1];
-    const int ks = recover_control(a.m, z[2 * t + 2] - zx, z[2 * t + 3] - zy);
-    if (ks < 0) continue;
-    const float ax = zx - gx, bx = ax - zx;
-    const float ax_lo = (zx - (ax - bx)) + (-gx - bx);
-    const float ay = zy - gy, by = ay - zy;
-    const float ay_lo = (zy - (ay - by)) + (-gy - by);
-    const float D2 = fmaf(ax, ax, ay * ay);
-    const float D = fast_sqrt(D2);
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-      if (KT == 0 && k >= K) break;
-      const float corr = fmaf(2.f * ax_lo, a.m.sx[k], fmaf(2.f * ay_lo, a.m.sy[k], a.m.s2[k]));
-      const float nk = fmaf(ax + ax, a.m.sx[k], fmaf(ay + ay, a.m.sy[k], corr));
+  double* ab = dyn + tid;
+  float* wl = reinterpret_cast<float*>(dyn + (size_t)B * nthr) + gl;
+  for (int b = tid; b < B; b += nthr) beta[b] = expf(lb[b]);
+  for (int i = tid; i < B * gn; i += nthr) {
+    const int b = i / gn, q = i - b * gn;
+    reinterpret_cast<float*>(dyn + (size_t)B * nthr)[b * 64 + q] =
+        (float)dLL[((size_t)n * B + b) * a.G + g0 + q];
+  }
+  for (int b = 0; b < B; ++b) ab[b * nthr] = 0.0;
+  load_steps(a.m, st);
+  double agx = 0.0, agy = 0.0;
+  for (int t0 = 0; t0 < len; t0 += kStepBuf) {
+    const int tn = min(kStepBuf, len - t0);
+    __syncthreads();
+    recover_steps(a.m, z, t0, tn, ks);
+    __syncthreads();
+    for (int i = wave * sh.L + sub; i < tn; i += W * sh.L) {
+      const int kc = ks[i];
+      if (!on || kc == 255) continue;
+      asm volatile("" ::: "memory");   // the table stays in LDS, as in the forward
+      const float zx = z[2 * (t0 + i)], zy = z[2 * (t0 + i) + 1];
+      const float ax = zx - gx, bx = ax - zx;
+      const float ax_lo = (zx - (ax - bx)) + (-gx - bx);
+      const float ay = zy - gy, by = ay - zy;
+      const float ay_lo = (zy - (ay - by)) + (-gy - by);
+      const float D2 = fmaf(ax, ax, ay * ay);
+      const float D = fast_sqrt(D2);
+      const float4 own = st[kc];
+      const float sxs = own.x, sys = own.y;
       // hardware square root and reciprocal, as in the forward's fixed-K path
-      dk[k] = fast_sqrt(fmaxf(D2 + nk, 0.f));
-      dl[k] = nk * fast_rcp(dk[k] + D);
-    }
-    if constexpr (KT > 0) {
-      const float ds = dk[ks], dls = dl[ks], sxs = a.m.sx[ks], sys = a.m.sy[ks];
-      // the unit vectors take hardware reciprocals (within 1 ulp) in place of
-      // IEEE divisions, one per heading instead of three (11 % of the kernel's
-      // time at K = 32); the gradient's error bar is 1e-5 of its norm
-      const float rds = ds > 0.f ? __builtin_amdgcn_rcpf(ds) : 0.f;
-      const float sxs_ds = sxs * rds, sys_ds = sys * rds;
-      // yhat_k - yhat_* once per heading (independent of beta; yhat := 0 where
-      // the distance is 0), and max_k (-beta dl_k) = -beta min_k dl_k exactly
-      // (the rounded product is monotone in dl_k)
-      float ux[KM], uy[KM];
-      float dmin = INFINITY;
-#pragma unroll
-      for (int k = 0; k < KM; ++k) {
-        const float rk = __builtin_amdgcn_rcpf(dk[k]);
-        if (dk[k] > 0.f && ds > 0.f) {
-          const float v = (dls - dl[k]) * (rk * rds);
-          ux[k] = fmaf(ax, v, fmaf(a.m.sx[k], rk, -sxs_ds));
-          uy[k] = fmaf(ay, v, fmaf(a.m.sy[k], rk, -sys_ds));
-        } else if (dk[k] > 0.f) {
-          ux[k] = (ax + a.m.sx[k]) * rk;
-          uy[k] = (ay + a.m.sy[k]) * rk;
-        } else if (ds > 0.f) {
-          ux[k] = -(ax + sxs) * rds;
-          uy[k] = -(ay + sys) * rds;
-        } else {
-          ux[k] = 0.f;
-          uy[k] = 0.f;
-        }
-        dmin = fminf(dmin, dl[k]);
-      }
-      for (int b = 0; b < B; ++b) {
-        const float nbt = -beta[b];
-        // base-2 exponents with the shift folded into one FMA (p is a ratio,
-        // so the shift's rounding cancels)
-        const float nb2 = nbt * kLog2e, mx2 = nb2 * dmin;
-        float s = 0.f, ex = 0.f, ey = 0.f, ed = 0.f;
+      auto delta = [&](float sx, float sy, float s2, float* d) {
+        const float corr = fmaf(2.f * ax_lo, sx, fmaf(2.f * ay_lo, sy, s2));
+        const float nk = fmaf(ax + ax, sx, fmaf(ay + ay, sy, corr));
+        *d = fast_sqrt(fmaxf(D2 + nk, 0.f));
+        return nk * fast_rcp(*d + D);
+      };
+      float ds;
+      float dls = delta(sxs, sys, own.z, &ds);
+      if constexpr (KT > 0) {
+        float dl[KM], cf[KM];
+        float dmin = INFINITY;
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
-          const float p = fast_exp2(fmaf(nb2, dl[k], -mx2));
-          s += p;
-          ex = fmaf(p, ux[k], ex);
-          ey = fmaf(p, uy[k], ey);
-          ed = fmaf(p, dl[k] - dls, ed);
+          float d;
+          const float4 c = st[k];
+          dl[k] = delta(c.x, c.y, c.z, &d);
+          dmin = fminf(dmin, dl[k]);
         }
-        const float inv = 1.f / s;
-        // E[yhat] - yhat_* = ex/s ; E[Delta] - Delta_* = ed/s
-        agx += (double)(w[b] * (nbt * (ex * inv)));
-        agy += (double)(w[b] * (nbt * (ey * inv)));
-        ab[b] += (double)(w[b] * (beta[b] * (ed * inv)));
-      }
-    } else {
-      // any K: per (beta, heading), without per-heading arrays beyond dl and dk
-      const float ds = dk[ks];
-      for (int b = 0; b < B; ++b) {
-        const float nbt = -beta[b];
-        float mx = -INFINITY;
-        for (int k = 0; k < K; ++k) mx = fmaxf(mx, nbt * dl[k]);
-        float s = 0.f, ex = 0.f, ey = 0.f, ed = 0.f;
-        for (int k = 0; k < K; ++k) {
-          const float p = exp_nonpos(nbt * dl[k] - mx);
-          s += p;
-          // yhat_k - yhat_*  (yhat := 0 where the distance is 0)
-          float ux, uy;
-          if (dk[k] > 0.f && ds > 0.f) {
-            const float v = (dl[ks] - dl[k]) / (dk[k] * ds);
-            ux = fmaf(ax, v, a.m.sx[k] / dk[k] - a.m.sx[ks] / ds);
-            uy = fmaf(ay, v, a.m.sy[k] / dk[k] - a.m.sy[ks] / ds);
-          } else if (dk[k] > 0.f) {
-            ux = (ax + a.m.sx[k]) / dk[k];
-            uy = (ay + a.m.sy[k]) / dk[k];
-          } else if (ds > 0.f) {
-            ux = -(ax + a.m.sx[ks]) / ds;
-            uy = -(ay + a.m.sy[ks]) / ds;
-          } else {
-            ux = 0.f;
-            uy = 0.f;
+        dls -= dmin;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+          dl[k] -= dmin;
+          cf[k] = 0.f;
+        }
+        float csum = 0.f;
+        for (int b = 0; b < B; ++b) {
+          const float be = beta[b], nb2 = -be * kLog2e, w = wl[b * 64];
+          float p[KM];
+          float s = 0.f, ed = 0.f;
+#pragma unroll
+          for (int k = 0; k < KM; ++k) {
+            p[k] = fast_exp2(nb2 * dl[k]);
+            s += p[k];
+            ed = fmaf(p[k], dl[k], ed);
           }
-          ex = fmaf(p, ux, ex);
-          ey = fmaf(p, uy, ey);
-          ed = fmaf(p, dl[k] - dl[ks], ed);
+          const float inv = 1.f / s;
+          // d log beta: beta (E[Delta] - Delta_*)
+          ab[b * nthr] += (double)(w * (be * fmaf(ed, inv, -dls)));
+          const float c = -(w * be) * inv;
+#pragma unroll
+          for (int k = 0; k < KM; ++k) cf[k] = fmaf(c, p[k], cf[k]);
         }
-        const float inv = 1.f / s;
-        // E[yhat] - yhat_* = ex/s ; E[Delta] - Delta_* = ed/s
-        agx += (double)(w[b] * (nbt * (ex * inv)));
-        agy += (double)(w[b] * (nbt * (ey * inv)));
-        ab[b] += (double)(w[b] * (beta[b] * (ed * inv)));
+        // sum_k cf_k (yhat_k - yhat_*): d_k = D + Delta_k (yhat := 0 where the
+        // distance is 0; the sum errs by some 1e-7 D, so 0 means below 1e-5 D)
+        const float base = D + dmin, zero = 1e-5f * D;
+        const float rds = ds > zero ? fast_rcp(ds) : 0.f;
+        const float sxs_ds = sxs * rds, sys_ds = sys * rds;
+        float ex = 0.f, ey = 0.f;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+          const float4 c = st[k];
+          const float d = base + dl[k];
+          const float rk = d > zero ? fast_rcp(d) : 0.f;
+          float ux, uy;
+          if (d > zero && ds > zero) {
+            const float v = (dls - dl[k]) * (rk * rds);
+            ux = fmaf(ax, v, fmaf(c.x, rk, -sxs_ds));
+            uy = fmaf(ay, v, fmaf(c.y, rk, -sys_ds));
+          } else {
+            ux = (ax + c.x) * rk - (ax + sxs) * rds;
+            uy = (ay + c.y) * rk - (ay + sys) * rds;
+          }
+          ex = fmaf(cf[k], ux, ex);
+          ey = fmaf(cf[k], uy, ey);
+        }
+        agx += (double)ex;
+        agy += (double)ey;
+      } else {
+        // any K: per (beta, heading), without per-heading arrays beyond dl and dk
+        float dl[KM], dk[KM];
+        for (int k = 0; k < K; ++k) dl[k] = delta(a.m.sx[k], a.m.sy[k], a.m.s2[k], dk + k);
+        for (int b = 0; b < B; ++b) {
+          const float be = beta[b], nbt = -be, w = wl[b * 64];
+          float mx = -INFINITY;
+          for (int k = 0; k < K; ++k) mx = fmaxf(mx, nbt * dl[k]);
+          float s = 0.f, ex = 0.f, ey = 0.f, ed = 0.f;
+          for (int k = 0; k < K; ++k) {
+            const float p = exp_nonpos(nbt * dl[k] - mx);
+            s += p;
+            // yhat_k - yhat_*  (yhat := 0 where the distance is 0)
+            float ux, uy;
+            if (dk[k] > 0.f && ds > 0.f) {
+              const float v = (dls - dl[k]) / (dk[k] * ds);
+              ux = fmaf(ax, v, a.m.sx[k] / dk[k] - sxs / ds);
+              uy = fmaf(ay, v, a.m.sy[k] / dk[k] - sys / ds);
+            } else if (dk[k] > 0.f) {
+              ux = (ax + a.m.sx[k]) / dk[k];
+              uy = (ay + a.m.sy[k]) / dk[k];
+            } else if (ds > 0.f) {
+              ux = -(ax + sxs) / ds;
+              uy = -(ay + sys) / ds;
+            } else {
+              ux = 0.f;
+              uy = 0.f;
+            }
+            ex = fmaf(p, ux, ex);
+            ey = fmaf(p, uy, ey);
+            ed = fmaf(p, dl[k] - dls, ed);
+          }
+          const float inv = 1.f / s;
+          // E[yhat] - yhat_* = ex/s ; E[Delta] - Delta_* = ed/s
+          agx += (double)(w * (nbt * (ex * inv)));
+          agy += (double)(w * (nbt * (ey * inv)));
+          ab[b * nthr] += (double)(w * (be * (ed * inv)));
+        }
       }
     }
   }
-  const double sgx = group_sum(agx, lg), sgy = group_sum(agy, lg);
-  if (it.on && it.sub == 0) {
-    ws_g[((size_t)n * a.G + g) * 2] = sgx;
-    ws_g[((size_t)n * a.G + g) * 2 + 1] = sgy;
+  const double sgx = goal_sum(agx, sub, sh.L), sgy = goal_sum(agy, sub, sh.L);
+  if (on && sub == 0) {
+    red[wave][2 * gl] = sgx;
+    red[wave][2 * gl + 1] = sgy;
   }
-  for (int b = 0; b < B; ++b) {
-    const double s = group_sum(ab[b], lg);
-    if (it.on && it.sub == 0) ws_b[((size_t)n * a.G + g) * B + b] = s;
+  __syncthreads();
+  for (int i = tid; i < 2 * gn; i += nthr) {
+    double s = red[0][i];
+    for (int w = 1; w < W; ++w) s += red[w][i];
+    ws_g[((size_t)n * a.G + g0) * 2 + i] = s;
+  }
+  // d log beta of the slice: a wave per beta sums the threads' entries
+  for (int b = wave; b < B; b += W) {
+    double s = 0.0;
+    for (int i = lane; i < nthr; i += 64) s += dyn[(size_t)b * nthr + i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) ws_b[((size_t)n * gridDim.y + blockIdx.y) * B + b] = s;
   }
 }
 
 // Fixed-order second stage.  Long sums -- the goals over tracks, a shared log
-// beta over (track, goal) -- take one block per output: thread t adds terms
+// beta over (track, slice) -- take one block per output: thread t adds terms
 // t, t + 256, ... in ascending order, then a fixed tree combines the 256
-// partials.  Per-track log beta (a sum over the goals only) takes one thread
+// partials.  Per-track log beta (a sum over the slices only) takes one thread
 // per output.  Every order is fixed, so results are bitwise reproducible.
 constexpr int kSumThreads = 256;
 
 __global__ void __launch_bounds__(kSumThreads)
-    loglik_sum_kernel(int N, int G, int B, const double* __restrict__ ws_g,
+    loglik_sum_kernel(int N, int G, int B, int slices, const double* __restrict__ ws_g,
                       const double* __restrict__ ws_b, double* __restrict__ dgoals,
                       double* __restrict__ dlog_beta) {
-  __shared__ double red[kSumThreads];
+  __shared__ double red[kSumThreads / 64];
   const int o = blockIdx.x;
+  const bool goal = o < 2 * G;
+  const double* src = goal ? ws_g + o : ws_b + (o - 2 * G);
+  const size_t stride = goal ? (size_t)2 * G : (size_t)B;
+  const int total = goal ? N : N * slices;
   double s = 0.0;
-  if (o < 2 * G) {
-    const int g = o >> 1, c = o & 1;
-    for (int n = threadIdx.x; n < N; n += kSumThreads) s += ws_g[((size_t)n * G + g) * 2 + c];
-  } else {
-    const int jb = o - 2 * G;
-    const int total = N * G;  // term i = n G + g
-    for (int i = threadIdx.x; i < total; i += kSumThreads) s += ws_b[(size_t)i * B + jb];
-  }
-  red[threadIdx.x] = s;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < total; i += kSumThreads) s += src[(size_t)i * stride];
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int w = kSumThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    if (o < 2 * G) dgoals[o] = red[0];
-    else dlog_beta[o - 2 * G] = red[0];
+    s = red[0];
+    for (int w = 1; w < kSumThreads / 64; ++w) s += red[w];
+    if (goal) dgoals[o] = s;
+    else dlog_beta[o - 2 * G] = s;
   }
 }
 
-__global__ void loglik_track_beta_kernel(int N, int G, int B, const double* __restrict__ ws_b,
+__global__ void loglik_track_beta_kernel(int N, int B, int slices,
+                                         const double* __restrict__ ws_b,
                                          double* __restrict__ dlog_beta) {
   const int jb = blockIdx.x * blockDim.x + threadIdx.x;
   if (jb >= N * B) return;
   const int n = jb / B, b = jb - n * B;
   double s = 0.0;
-  for (int g = 0; g < G; ++g) s += ws_b[((size_t)n * G + g) * B + b];
+  for (int q = 0; q < slices; ++q) s += ws_b[((size_t)n * slices + q) * B + b];
   dlog_beta[jb] = s;
 }
 
-// log2 of the lanes per (track, goal) for a launch.  Fewer lanes per goal
-// leave fewer idle in a track's last pass over its steps (200 steps: 78 % of
-// the lanes busy at 64 lanes per goal, 89 % at 32, 96 % at 16) but make fewer
-// waves.  Each width is scored by its busy fraction (from Tmax, and the goal
-// slots the last wave of a track leaves empty) times the fraction of
-// `target_waves` resident wave slots its waves fill; ties keep the wider form.
-static int ll_lanes_log2(int N, int G, int Tmax, double target_waves) {
-  int best = 6;
-  double best_score = -1.0;
-  for (int lg = 6; lg >= 3; --lg) {
-    const int L = 1 << lg, gpw = 64 >> lg;
-    const long groups = (G + gpw - 1) / gpw;
-    const double waves = (double)N * (double)groups;
-    const double passes = Tmax > 0 ? (double)((Tmax + L - 1) / L) : 1.0;
-    const double busy = (Tmax > 0 ? Tmax / (L * passes) : 1.0) * ((double)G / ((double)groups * gpw));
-    const double score = busy * std::min(1.0, waves / target_waves);
-    if (score > best_score + 1e-9) {
-      best = lg;
-      best_score = score;
-    }
-  }
-  return best;
+// Lanes per goal and goals per slice.  At most 21 goals a slice, so that each
+// keeps at least three lanes (60 or more of the 64 busy); more slices than that
+// only while the tracks leave CUs without a block (each slice recovers the
+// track's controls again).
+static LLShape ll_shape(int N, int G) {
+  const int fill = std::min(G, (256 + std::max(N, 1) - 1) / std::max(N, 1));
+  const int slices = std::max((G + 20) / 21, fill);
+  const int per = (G + slices - 1) / slices;
+  return LLShape{64 / per, per};
 }
 
-// Resident wave slots of the device's 1024 SIMDs (256 CUs x 4) at each
-// kernel's occupancy: the forward holds four waves per SIMD at every K; the
-// adjoint two at K = 32 (247 VGPRs), three at K = 16 and in the any-K build
-// (kt = 0), four at K <= 8.
-constexpr double kSimds = 1024.0;
-static double ll_forward_waves() { return 4.0 * kSimds; }
-static double ll_backward_waves(int kt) {
-  return (kt == 32 ? 2.0 : kt == 16 || kt == 0 ? 3.0 : 4.0) * kSimds;
+// Waves per block: four (one per SIMD), or more for the chunks of steps while
+// the tracks alone leave the device's wave slots unfilled -- always whole fours:
+// a block's waves go to the SIMDs in turn, so five of them crowd one SIMD (five
+// rounds instead of seven, but 102 us instead of 90 forward and 242 instead of 152
+// in the adjoint at 1024 tracks).
+static int ll_waves(int64_t blocks, int Tmax, int L, int most) {
+  const int chunks = std::max(1, (Tmax + L - 1) / L);
+  int w = 4;
+  while (w < most && w < chunks && blocks * w < 4096) w *= 2;
+  return std::min(w, (chunks + 3) & ~3);
 }
 
 static cap_status make_ll_args(int32_t K, double speed, double dt, const float* tracks,
@@ -318,7 +384,7 @@ static cap_status make_ll_args(int32_t K, double speed, double dt, const float* 
   if (N < 0 || Tmax < 0) return fail(CAP_E_INVALID, "N and Tmax must be >= 0");
   if (G < 1 || G > CAP_MAX_G || B < 1 || B > CAP_MAX_B)
     return fail(CAP_E_INVALID, "G in [1, 64] and B in [1, 16] required");
-  // one wave (64 threads) per (track, goal) at most: thread indices stay in int
+  // term counts and thread indices stay in int
   if ((int64_t)N * G > ((int64_t)1 << 25)) return fail(CAP_E_INVALID, "N * G above 2^25");
   if (N > 0 && (!tracks || !lengths || !goals || !log_beta))
     return fail(CAP_E_INVALID, "tracks/lengths/goals/log_beta is NULL");
@@ -349,17 +415,19 @@ extern "C" cap_status cap_loglik(int32_t K, double speed, double dt, const float
   if (st != CAP_OK) return st;
   if (N == 0) return CAP_OK;
   if (!LL_dev) return fail(CAP_E_INVALID, "LL is NULL");
-  const int lg = ll_lanes_log2(N, G, Tmax, ll_forward_waves());
-  const int gpw = 64 >> lg, per_block = kLLThreads / 64;
-  const long waves = (long)N * ((G + gpw - 1) / gpw);
-  const dim3 grid((unsigned)((waves + per_block - 1) / per_block)), block(kLLThreads);
+  const LLShape lg = ll_shape(N, G);
+  const int slices = (G + lg.slice - 1) / lg.slice;
+  int W = ll_waves((int64_t)N * slices, Tmax, lg.L, 16);
+  while (W > 4 && W * B * (64 + lg.slice) > 12288) W -= 4;   // sums within 96 KiB of LDS
+  const dim3 grid((unsigned)N, (unsigned)slices), block(64 * W);
+  const size_t lds = (size_t)W * (64 + lg.slice) * B * sizeof(double);
   hipStream_t s = as_stream(stream);
   switch (a.m.U) {
-    case 4: hipLaunchKernelGGL(loglik_kernel<4>, grid, block, 0, s, a, lg, LL_dev); break;
-    case 8: hipLaunchKernelGGL(loglik_kernel<8>, grid, block, 0, s, a, lg, LL_dev); break;
-    case 16: hipLaunchKernelGGL(loglik_kernel<16>, grid, block, 0, s, a, lg, LL_dev); break;
-    case 32: hipLaunchKernelGGL(loglik_kernel<32>, grid, block, 0, s, a, lg, LL_dev); break;
-    default: hipLaunchKernelGGL(loglik_kernel<0>, grid, block, 0, s, a, lg, LL_dev); break;
+    case 4: hipLaunchKernelGGL(loglik_kernel<4>, grid, block, lds, s, a, lg, LL_dev); break;
+    case 8: hipLaunchKernelGGL(loglik_kernel<8>, grid, block, lds, s, a, lg, LL_dev); break;
+    case 16: hipLaunchKernelGGL(loglik_kernel<16>, grid, block, lds, s, a, lg, LL_dev); break;
+    case 32: hipLaunchKernelGGL(loglik_kernel<32>, grid, block, lds, s, a, lg, LL_dev); break;
+    default: hipLaunchKernelGGL(loglik_kernel<0>, grid, block, lds, s, a, lg, LL_dev); break;
   }
   CAP_HIP(hipGetLastError());
   return CAP_OK;
@@ -381,28 +449,30 @@ static cap_status loglik_backward_launch(const LLArgs& a, int32_t per_track_beta
   const int32_t N = a.N, G = a.G, B = a.B;
   double* ws_g = static_cast<double*>(ws_dev);
   double* ws_b = ws_g + (size_t)N * G * 2;
+  const LLShape lg = ll_shape(N, G);
+  const int slices = (G + lg.slice - 1) / lg.slice;
   if (N > 0) {
     const int kt = a.m.K == 4 || a.m.K == 8 || a.m.K == 16 || a.m.K == 32 ? a.m.K : 0;
-    const int lg = ll_lanes_log2(N, G, a.Tmax, ll_backward_waves(kt));
-    const int gpw = 64 >> lg, per_block = kLLThreads / 64;
-    const long waves = (long)N * ((G + gpw - 1) / gpw);
-    const dim3 grid((unsigned)((waves + per_block - 1) / per_block)), block(kLLThreads);
+    int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, 16);
+    while (W > 4 && W * B > 192) W -= 4;   // sums within 96 KiB of LDS
+    const dim3 grid((unsigned)N, (unsigned)slices), block(64 * W);
+    const size_t lds = (size_t)B * (64 * W * sizeof(double) + 64 * sizeof(float));
     switch (kt) {
-      case 4: hipLaunchKernelGGL(loglik_backward_kernel<4>, grid, block, 0, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 8: hipLaunchKernelGGL(loglik_backward_kernel<8>, grid, block, 0, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 16: hipLaunchKernelGGL(loglik_backward_kernel<16>, grid, block, 0, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 32: hipLaunchKernelGGL(loglik_backward_kernel<32>, grid, block, 0, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      default: hipLaunchKernelGGL(loglik_backward_kernel<0>, grid, block, 0, s, a, lg, dLL_dev, ws_g, ws_b); break;
+      case 4: hipLaunchKernelGGL(loglik_backward_kernel<4>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
+      case 8: hipLaunchKernelGGL(loglik_backward_kernel<8>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
+      case 16: hipLaunchKernelGGL(loglik_backward_kernel<16>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
+      case 32: hipLaunchKernelGGL(loglik_backward_kernel<32>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
+      default: hipLaunchKernelGGL(loglik_backward_kernel<0>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
     }
     CAP_HIP(hipGetLastError());
   }
   // with N = 0 the sums are empty: the kernels write zeros
   const int long_sums = 2 * G + (per_track_beta ? 0 : B);
-  hipLaunchKernelGGL(loglik_sum_kernel, dim3(long_sums), dim3(kSumThreads), 0, s, N, G, B, ws_g,
-                     ws_b, dgoals_dev, dlog_beta_dev);
+  hipLaunchKernelGGL(loglik_sum_kernel, dim3(long_sums), dim3(kSumThreads), 0, s, N, G, B, slices,
+                     ws_g, ws_b, dgoals_dev, dlog_beta_dev);
   if (per_track_beta && N > 0)
-    hipLaunchKernelGGL(loglik_track_beta_kernel, dim3((N * B + 255) / 256), dim3(256), 0, s, N, G,
-                       B, ws_b, dlog_beta_dev);
+    hipLaunchKernelGGL(loglik_track_beta_kernel, dim3((N * B + 255) / 256), dim3(256), 0, s, N, B,
+                       slices, ws_b, dlog_beta_dev);
   CAP_HIP(hipGetLastError());
   return CAP_OK;
 }
@@ -476,8 +546,8 @@ extern "C" cap_status cap_loglik_backward_noalloc(int32_t K, double speed, doubl
   void* scratch = nullptr;
   st = scratch_of_current_device(&scratch);
   if (st != CAP_OK) return st;
-  // every partial-sum slot the launches read is written first (one per (track,
-  // goal) item), so the previous call's contents need no clearing
+  // every partial-sum slot the launches read is written first (one per track
+  // and goal or slice), so the previous call's contents need no clearing
   return loglik_backward_launch(a, per_track_beta, dLL_dev, dgoals_dev, dlog_beta_dev, scratch,
                                 as_stream(stream));
 }
