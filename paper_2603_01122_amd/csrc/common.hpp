@@ -551,4 +551,169 @@ __device__ __forceinline__ int draw_control(float ax, float ay, float ib, float 
   return ss * KT + cdf_index<KT>(C, thr, KT);
 }
 
+// ---------------------------------------------------------------- wide draws
+// draw_control (unshifted) of one particle by L = 4 or 8 neighbouring lanes, for
+// launches whose particles leave the device idle: with one lane per particle a
+// step is one lane's S KT controls in series, at one wave per SIMD 5 us a step
+// for 96 controls; by 8 lanes 2.1 us (8192 particles x 10 steps of 6 x 16
+// controls, the whole launch 52 -> 34 us).  The chain of S KT dependent additions,
+// 8-10 cycles each with so few waves, is what remains.  Lane `sub` forms the weights of the heading pairs k, k + KT/2
+// with k = sub, sub + L, ... of every speed, by draw_control's operations; the
+// prefix sums then run over the lanes in control order (each addition takes its
+// weight from the lane that holds it by a DPP move in the same instruction), so
+// the sums, and the control, are draw_control's bit for bit.  At L = 8 the
+// running sums are those of the group's first quad, which sees the second quad's
+// weights mirrored.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __uint_as_float(
+      (uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+
+// Calls f(weight of lane j) for the L lanes of the group in order.
+template <int L, class F>
+__device__ __forceinline__ void in_lane_order(float w, F f) {
+  f(dpp_f<0x00>(w));
+  f(dpp_f<0x55>(w));
+  f(dpp_f<0xAA>(w));
+  f(dpp_f<0xFF>(w));
+  if constexpr (L == 8) {
+    const float m = dpp_f<0x141>(w);   // lane i of the first quad: lane 7 - i's
+    f(dpp_f<0xFF>(m));
+    f(dpp_f<0xAA>(m));
+    f(dpp_f<0x55>(m));
+    f(dpp_f<0x00>(m));
+  }
+}
+
+// The first quad's value in both.
+template <int L>
+__device__ __forceinline__ int from_first_quad(int v, int sub) {
+  if constexpr (L == 8) {
+    const int m = __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);
+    return sub < 4 ? v : m;
+  }
+  return v;
+}
+
+// This lane's rows of the control table for its NP heading pairs, by speed, in
+// registers where they are few (one pair); else the draw reads them from ctl.
+template <int KT, int L>
+struct WideRows {
+  static constexpr int NP = KT / 2 / L;      // heading pairs of a lane
+  static_assert(NP * L * 2 == KT, "whole pairs per lane");
+  static constexpr bool kHeld = NP == 1;
+  float x[kHeld ? CAP_MAX_S : 1][NP], y[kHeld ? CAP_MAX_S : 1][NP], z[kHeld ? CAP_MAX_S : 1][NP];
+  __device__ __forceinline__ void load(const float4* ctl, int S, int sub) {
+    if constexpr (kHeld)
+#pragma unroll
+      for (int s = 0; s < CAP_MAX_S; ++s)
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          const float4 c = ctl[min(s, S - 1) * KT + sub + L * i];
+          x[s][i] = c.x;
+          y[s][i] = c.y;
+          z[s][i] = c.z;
+        }
+  }
+};
+
+// Every lane of the wave must call it; ctl as for draw_control.
+template <int KT, int L>
+__device__ __forceinline__ int wide_control(float ax, float ay, float ib, float u, int S,
+                                            uint32_t smask, int s_last,
+                                            const WideRows<KT, L>& rows, const float4* ctl,
+                                            int sub) {
+  constexpr int NP = WideRows<KT, L>::NP;
+  constexpr bool kHeld = WideRows<KT, L>::kHeld;
+  const float D2 = fmaf(ax, ax, ay * ay);
+  const float D = fast_sqrt(D2);
+  const float Dib = D * ib;
+  const float ax2 = ax + ax, ay2 = ay + ay;
+  // weights of the opposite headings (fx, fy) and (-fx, -fy)
+  const auto weights = [&](float fx, float fy, float s2, float* wp, float* wm) {
+    const float dot = fmaf(ax2, fx, ay2 * fy);
+    const float np = s2 + dot, nm = s2 - dot;
+    const float dp = fast_sqrt(fabsf(D2 + np)), dm = fast_sqrt(fabsf(D2 + nm));
+    *wp = fast_exp2(np * fast_rcp(fmaf(dp, ib, Dib)));
+    *wm = fast_exp2(nm * fast_rcp(fmaf(dm, ib, Dib)));
+  };
+  // Two speeds at a time, without a branch between them: the second one's weights
+  // fill the waits of the first one's chain of additions.  A speed that is not
+  // allowed adds zeros.
+  float wp[CAP_MAX_S][NP], wm[CAP_MAX_S][NP];
+  float bs[CAP_MAX_S];
+  float acc = 0.f;
+#pragma unroll
+  for (int s0 = 0; s0 < CAP_MAX_S; s0 += 2) {
+    if (s0 < S) {
+#pragma unroll
+      for (int s = s0; s < s0 + 2; ++s) {
+        const bool allowed = s < S && ((smask >> s) & 1u);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          if constexpr (kHeld) {
+            weights(rows.x[s][i], rows.y[s][i], rows.z[s][i], &wp[s][i], &wm[s][i]);
+          } else {
+            const float4 c = ctl[min(s, S - 1) * KT + sub + L * i];
+            weights(c.x, c.y, c.z, &wp[s][i], &wm[s][i]);
+          }
+          wp[s][i] = allowed ? wp[s][i] : 0.f;
+          wm[s][i] = allowed ? wm[s][i] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int s = s0; s < s0 + 2; ++s) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) in_lane_order<L>(wp[s][i], [&](float w) { acc += w; });
+#pragma unroll
+        for (int i = 0; i < NP; ++i) in_lane_order<L>(wm[s][i], [&](float w) { acc += w; });
+        bs[s] = acc;
+      }
+    } else {
+#pragma unroll
+      for (int s = s0; s < s0 + 2; ++s) {
+        bs[s] = acc;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) wp[s][i] = wm[s][i] = 0.f;
+      }
+    }
+  }
+  const float thr = u * acc;
+  int ss = 0;
+  float prev = 0.f;
+#pragma unroll
+  for (int s = 0; s < CAP_MAX_S - 1; ++s) {
+    const bool right = s < s_last && bs[s] <= thr;
+    ss += right ? 1 : 0;
+    prev = right ? bs[s] : prev;
+  }
+  ss = from_first_quad<L>(ss, sub);
+  if constexpr (kHeld) {
+#pragma unroll
+    for (int s = 1; s < CAP_MAX_S; ++s)
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        wp[0][i] = ss == s ? wp[s][i] : wp[0][i];
+        wm[0][i] = ss == s ? wm[s][i] : wm[0][i];
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const float4 c = ctl[ss * KT + sub + L * i];
+      weights(c.x, c.y, c.z, &wp[0][i], &wm[0][i]);
+    }
+  }
+  int count = 0, left = KT - 1;   // the last boundary is the next block's
+  const auto step = [&](float w) {
+    prev += w;
+    if (left-- > 0) count += prev <= thr ? 1 : 0;
+  };
+#pragma unroll
+  for (int i = 0; i < NP; ++i) in_lane_order<L>(wp[0][i], step);
+#pragma unroll
+  for (int i = 0; i < NP; ++i) in_lane_order<L>(wm[0][i], step);
+  return ss * KT + from_first_quad<L>(count, sub);
+}
+
 }  // namespace capred

@@ -320,7 +320,7 @@ __device__ __forceinline__ int slot_of_kind_tile(const SlotDev* sl, int n_active
   return lo;
 }
 
-template <int KT, int P, bool SHIFT, bool MS>
+template <int KT, int P, bool SHIFT, bool MS, int L = 1>
 __global__ void __launch_bounds__(1024)
     plan_rollout_kernel(const uint8_t* __restrict__ base, uint32_t* __restrict__ queues, int cap) {
   __shared__ TileShared sh;
@@ -365,19 +365,19 @@ __global__ void __launch_bounds__(1024)
     if (kind < 0) break;
     const int local = __builtin_amdgcn_readfirstlane(s_tile[1]);
     const int s = __builtin_amdgcn_readfirstlane(slot_of_kind_tile(sl, H->n_active, kind, local));
-    const int per = (int)blockDim.x * (P >> kind);
+    const int per = (int)blockDim.x / L * (P >> kind);
     const int64_t first = sl[s].kt_first[kind] + (int64_t)(local - sl[s].kt_begin[kind]) * per;
     // rollout_tile starts and ends with a barrier: s_tile is not rewritten
     // before every thread has read it.  The host only makes kinds whose size
     // P >> kind is at least one particle per thread.
     if (kind == 0) {
-      rollout_tile<KT, P, SHIFT, MS>(sl[s].rd, first, H->seed_lo, H->seed_hi, sh, win, cap, ctl);
+      rollout_tile<KT, P, SHIFT, MS, L>(sl[s].rd, first, H->seed_lo, H->seed_hi, sh, win, cap, ctl);
     } else if constexpr (P >= 2) {
       if (kind == 1 || P == 2)
-        rollout_tile<KT, P / 2, SHIFT, MS>(sl[s].rd, first, H->seed_lo, H->seed_hi, sh, win, cap,
+        rollout_tile<KT, P / 2, SHIFT, MS, L>(sl[s].rd, first, H->seed_lo, H->seed_hi, sh, win, cap,
                                            ctl);
       else
-        rollout_tile<KT, (P >= 4 ? P / 4 : 1), SHIFT, MS>(sl[s].rd, first, H->seed_lo,
+        rollout_tile<KT, (P >= 4 ? P / 4 : 1), SHIFT, MS, L>(sl[s].rd, first, H->seed_lo,
                                                           H->seed_hi, sh, win, cap, ctl);
     }
   }
@@ -415,11 +415,20 @@ struct HostSlot {
   bool ent_full[4] = {true, true, true, true};                 // ring entry content unknown
 };
 
+// Rollout variants of a plan's launches: plain, shifted exponent, and (several
+// speeds) kWideLanes lanes per particle.
+constexpr int kVariants = 3, kWideVariant = 2, kWideLanes = 4;
+// Particles of a cycle up to which the wide variant runs: with four lanes each
+// they fill four waves on each SIMD; beyond, the lanes repeat the chain of
+// additions for nothing.  Five humans of 8192 particles x 6 steps, 96 controls:
+// rollout 92 -> 49 us.
+constexpr int64_t kWideParticles = 65536;
+
 struct Entry {
   uint32_t* queues = nullptr;   // this entry's tile counters and update tickets (device)
   uint8_t* dev = nullptr;       // header + slots
   uint8_t* host = nullptr;      // pinned mirror
-  hipGraphExec_t main[2] = {nullptr, nullptr};  // [shift variant]
+  hipGraphExec_t main[kVariants] = {};  // [rollout variant]
   hipEvent_t done = nullptr;
   bool pending = false;
 };
@@ -436,11 +445,11 @@ struct cap_plan {
   uint32_t* queues = nullptr;   // tile counters and update tickets of every ring entry (device)
   size_t entry_bytes = 0;
   int cap_words = 0;            // LDS window words per buffer
-  int grid_blocks[2] = {0, 0};  // persistent blocks per launch, per rollout variant
+  int grid_blocks[capred::kVariants] = {};  // persistent blocks per launch, per rollout variant
   int n_cus = 1;                // compute units of the device
   int smooth_blocks = 0;        // persistent blocks of the smoothing stage (0: no stage)
   int per_tile = 0;
-  const void* rollout_fn[2] = {nullptr, nullptr};      // [shift variant]
+  const void* rollout_fn[capred::kVariants] = {};              // [rollout variant] (wide: may be null)
   const void* rollout_one_fn[2] = {nullptr, nullptr};
   int last_variant = 0;
   hipStream_t cap_stream = nullptr;
@@ -465,6 +474,8 @@ static void pick_fns_p(const void** r, const void** one) {
   r[1] = (const void*)plan_rollout_kernel<KT, P, true, MS>;
   one[0] = (const void*)plan_rollout_one_kernel<KT, P, false, MS>;
   one[1] = (const void*)plan_rollout_one_kernel<KT, P, true, MS>;
+  if constexpr (MS && KT >= 2 * kWideLanes)
+    r[kWideVariant] = (const void*)plan_rollout_kernel<KT, P, false, MS, kWideLanes>;
 }
 
 template <int KT, bool MS>
@@ -517,7 +528,8 @@ static cap_status record_graphs(cap_plan* p, Entry& e) {
   const int minus1 = -1;
   // persistent rollout -> normalise, once per rollout variant (the clear runs
   // in the prelude launch before it)
-  for (int v = 0; v < 2; ++v) {
+  for (int v = 0; v < kVariants; ++v) {
+    if (!p->rollout_fn[v]) continue;
     CAP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     cap_status st = launch_rollout(p, e, v, s);
     hipLaunchKernelGGL(plan_normalize_kernel, dim3(4096), dim3(256), 0, s, (const uint8_t*)e.dev,
@@ -538,7 +550,7 @@ static cap_status record_graphs(cap_plan* p, Entry& e) {
 static void destroy_plan(cap_plan* p) {
   if (!p) return;
   for (auto& e : p->ring) {
-    for (int v = 0; v < 2; ++v)
+    for (int v = 0; v < kVariants; ++v)
       if (e.main[v]) (void)hipGraphExecDestroy(e.main[v]);
     if (e.done) (void)hipEventDestroy(e.done);
     if (e.dev) (void)hipFree(e.dev);
@@ -717,14 +729,18 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
     H->union_out = nullptr;
     H->union_H = H->union_nx = H->union_ny = 0;
   }
+  // several speeds: few particles take the wide variant
+  if (variant == 0 && p->rollout_fn[kWideVariant] && parts <= kWideParticles)
+    variant = kWideVariant;
   p->last_variant = variant;
   // tile kinds of the persistent launch
   {
-    const int nthr = p->cfg.block_threads, P = p->cfg.particles_per_thread;
+    const int unit = p->cfg.block_threads / (variant == kWideVariant ? kWideLanes : 1);
+    const int P = p->cfg.particles_per_thread;
     std::vector<int32_t> units(n);
     std::vector<int32_t> flat((size_t)n * kTileKinds);
     int32_t(*cnt)[kTileKinds] = reinterpret_cast<int32_t(*)[kTileKinds]>(flat.data());
-    for (int i = 0; i < n; ++i) units[i] = (int32_t)((out[i].rd.N + nthr - 1) / nthr);
+    for (int i = 0; i < n; ++i) units[i] = (int32_t)((out[i].rd.N + unit - 1) / unit);
     split_tiles(units.data(), n, P, std::max(1, p->grid_blocks[variant]), p->n_cus, cnt);
     int32_t kb = 0;
     for (int k = 0; k < kTileKinds; ++k) {
@@ -741,7 +757,7 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
       int32_t first = 0;
       for (int k = 0; k < kTileKinds; ++k) {
         out[i].kt_first[k] = first;
-        first += cnt[i][k] * nthr * std::max(1, P >> k);
+        first += cnt[i][k] * unit * std::max(1, P >> k);
       }
     }
     H->n_tiles = kb;
@@ -809,16 +825,20 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
   select_kernels(cfg.K, pc.S, cfg.particles_per_thread, p->rollout_fn, p->rollout_one_fn);
   const size_t dyn = window_lds_bytes(p->cap_words, p->per_tile);
   hipError_t e = hipSuccess;
-  for (int v = 0; v < 2; ++v) {
+  for (int v = 0; v < kVariants; ++v) {
+    if (!p->rollout_fn[v]) continue;
     e = hipFuncSetAttribute(p->rollout_fn[v], hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
     (void)e;  // not required on gfx950; the occupancy query below validates the size
   }
   // each variant's persistent grid fills the chip at that variant's own
   // occupancy (the shifted variant needs more registers)
-  int per_cu[2] = {0, 0};
-  for (int v = 0; v < 2 && e == hipSuccess; ++v)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[v], p->rollout_fn[v],
-                                                     cfg.block_threads, dyn);
+  int per_cu[kVariants] = {};
+  e = hipSuccess;
+  for (int v = 0; v < kVariants && e == hipSuccess; ++v)
+    if (p->rollout_fn[v])
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[v], p->rollout_fn[v],
+                                                       cfg.block_threads, dyn);
+  if (per_cu[kWideVariant] < 1) p->rollout_fn[kWideVariant] = nullptr;
   if (e != hipSuccess || per_cu[0] < 1 || per_cu[1] < 1) {
     destroy_plan(p);
     return e != hipSuccess ? hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor")
@@ -826,7 +846,7 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
   }
   const int cus = cap_device_cu_count();
   p->n_cus = std::max(1, cus);
-  for (int v = 0; v < 2; ++v)
+  for (int v = 0; v < kVariants; ++v)
     p->grid_blocks[v] = cfg.grid_blocks > 0 ? cfg.grid_blocks : std::max(1, cus) * per_cu[v];
   p->cfg.grid_blocks = p->grid_blocks[0];
   if (cfg.max_smooth_radius > 0) {

@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(256) normalize_kernel(const uint32_t* __restri
   for (size_t v = head * 4 + i; v < n; v += stride) p[v] = (float)c[v] / N;
 }
 
-template <int KT, int P, bool SHIFT, bool MS>
+template <int KT, int P, bool SHIFT, bool MS, int L>
 __global__ void __launch_bounds__(1024)
     rollout_plain_kernel(const RolloutDesc d, uint32_t seed_lo, uint32_t seed_hi, int cap) {
   __shared__ TileShared sh;
@@ -44,8 +44,8 @@ __global__ void __launch_bounds__(1024)
   extern __shared__ uint32_t win[];
   for (int i = threadIdx.x; i < 2 * cap; i += blockDim.x) win[i] = 0u;
   // the first barrier inside rollout_tile orders this clear before any binning
-  const int64_t first = (int64_t)blockIdx.x * P * blockDim.x;
-  rollout_tile<KT, P, SHIFT, MS>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
+  const int64_t first = (int64_t)blockIdx.x * P * (blockDim.x / L);
+  rollout_tile<KT, P, SHIFT, MS, L>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
 }
 
 // Track simulator: one thread per track, the same control draw as the rollout
@@ -137,19 +137,23 @@ static int plain_window_words(const RolloutDesc& d, int threads) {
   return std::max(64, (need + 3) & ~3);
 }
 
-template <int KT, int P, bool MS>
+template <int KT, int P, bool MS, int L = 1>
 static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t shi, int threads,
                                  hipStream_t s) {
-  const int64_t per_block = (int64_t)P * threads;
+  const int64_t per_block = (int64_t)P * (threads / L);
   const int64_t blocks = (d.N + per_block - 1) / per_block;
   const int cap = plain_window_words(d, threads);
   const size_t lds = window_lds_bytes(cap, P * threads);
-  if (d.shift)
-    hipLaunchKernelGGL((rollout_plain_kernel<KT, P, true, MS>), dim3((unsigned)blocks),
-                       dim3(threads), lds, s, d, slo, shi, cap);
-  else
-    hipLaunchKernelGGL((rollout_plain_kernel<KT, P, false, MS>), dim3((unsigned)blocks),
-                       dim3(threads), lds, s, d, slo, shi, cap);
+  if constexpr (L == 1) {
+    if (d.shift) {
+      hipLaunchKernelGGL((rollout_plain_kernel<KT, P, true, MS, 1>), dim3((unsigned)blocks),
+                         dim3(threads), lds, s, d, slo, shi, cap);
+      CAP_HIP(hipGetLastError());
+      return CAP_OK;
+    }
+  }
+  hipLaunchKernelGGL((rollout_plain_kernel<KT, P, false, MS, L>), dim3((unsigned)blocks),
+                     dim3(threads), lds, s, d, slo, shi, cap);
   CAP_HIP(hipGetLastError());
   return CAP_OK;
 }
@@ -167,6 +171,18 @@ static cap_status launch_plain_k(const RolloutDesc& d, uint32_t slo, uint32_t sh
                                  hipStream_t s) {
   const int64_t cus = std::max(1, cap_device_cu_count());
   const int64_t waves = (d.N + 64 * cus - 1) / (64 * cus);   // per CU
+  if constexpr (MS) {
+    // few particles: several lanes each, while those fit two (eight lanes) or four
+    // waves per SIMD; 8192 particles x 10 steps of 96 controls: 52 us by one lane,
+    // 34 by eight.
+    const auto threads = [&](int L) {
+      return 64 * (int)std::min<int64_t>((L * d.N + 64 * cus - 1) / (64 * cus), 16);
+    };
+    if constexpr (KT >= 16)
+      if (!d.shift && d.N <= 64 * cus) return launch_plain_t<KT, 1, MS, 8>(d, slo, shi, threads(8), s);
+    if constexpr (KT >= 8)
+      if (!d.shift && d.N <= 256 * cus) return launch_plain_t<KT, 1, MS, 4>(d, slo, shi, threads(4), s);
+  }
   if constexpr (!MS) {
     if (waves > 32) return launch_plain_t<KT, 4, MS>(d, slo, shi, 1024, s);
     if (waves > 16) return launch_plain_t<KT, 2, MS>(d, slo, shi, 1024, s);

@@ -163,7 +163,11 @@ __device__ __forceinline__ void sort_by_pair(int64_t first, int tile_n, int J, u
 // PAIR: draw the particles two at a time (draw_headings with M = 2), for fixed K of
 // at most 16 without the shifted exponent, where the two chains fit in the
 // registers of four waves per SIMD without spilling.
-template <int KT, int P, bool SHIFT, bool MS, bool PAIR>
+//
+// L > 1 (several speeds, K >= 2 L, not the shifted exponent): L neighbouring lanes
+// share a particle (wide_control); all carry its state, the first of them
+// emplaces it, and a tile holds P * blockDim.x / L particles.
+template <int KT, int P, bool SHIFT, bool MS, bool PAIR, int L>
 __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t first,
                                                   uint32_t seed_lo, uint32_t seed_hi,
                                                   TileShared& sh, uint32_t* win, int cap,
@@ -204,13 +208,14 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   // ---- per-particle (beta, g) draw, held for the whole horizon
   constexpr bool kFar = !SHIFT && !MS && (KT == 8 || KT == 16 || KT == 32);
   const uint32_t c3_pair = 2u * d.cycle, c3_head = 2u * d.cycle + 1u;
-  const int tile_n = (int)min((int64_t)P * nthr, (int64_t)d.N - first);   // particles of the tile
+  const int per = nthr / L;                                               // particles at a time
+  const int tile_n = (int)min((int64_t)P * per, (int64_t)d.N - first);    // particles of the tile
   uint32_t idx[P];
   int pair[P];
   bool act[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    const int local = p * nthr + tid;
+    const int local = p * per + tid / L;
     idx[p] = (uint32_t)first + (uint32_t)local;
     act[p] = local < tile_n;
     pair[p] = 0;
@@ -224,7 +229,7 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
         else lo = mid + 1;
       }
       pair[p] = lo < J ? lo : sh.last_pos;
-      if (d.trace_pair) as_global(d.trace_pair)[idx[p]] = pair[p];
+      if (d.trace_pair && tid % L == 0) as_global(d.trace_pair)[idx[p]] = pair[p];
     }
   }
   uint16_t* lists = reinterpret_cast<uint16_t*>(win + 2 * cap);
@@ -248,8 +253,10 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
       ib[p] = sh.ibeta[b];
       nbs[p] = -4.f * d.far.s4 / ib[p];
     }
+    act[p] = act[p] && tid % L == 0;   // from here on: emplaces a particle
   }
-
+  WideRows<(L > 1 ? KT : 2), L> rows;
+  if constexpr (L > 1) rows.load(ctl, d.S, tid % L);
   // The descriptor's fields that every step reads, in scalar registers for the
   // whole tile: it lies in memory that the loop's stores could alias, so each
   // use would be a load and a wait.
@@ -258,6 +265,8 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   uint32_t* const counts = d.counts;
   uint8_t* const trace_k = d.trace_k;
   const FarConst fc = d.far;
+  const int S = d.S, s_last = d.s_last;
+  const uint32_t smask = d.smask;
   const size_t plane = (size_t)nx * (size_t)ny;
   uint4 rw[P];
   const int list_cap = P * nthr;
@@ -298,8 +307,12 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
       for (int p = 0; p < P; ++p) {
         const float u = uniform24f(rw[p].x);
         rw[p] = make_uint4(rw[p].y, rw[p].z, rw[p].w, 0u);
-        const int k = draw_control<KT, SHIFT>((float)(X[p] - GXp[p]), (float)(Y[p] - GYp[p]),
-                                              ib[p], u, d.T, d.S, d.smask, d.s_last, ctl);
+        const float ax = (float)(X[p] - GXp[p]), ay = (float)(Y[p] - GYp[p]);
+        int k;
+        if constexpr (L > 1)
+          k = wide_control<KT, L>(ax, ay, ib[p], u, S, smask, s_last, rows, ctl, tid % L);
+        else
+          k = draw_control<KT, SHIFT>(ax, ay, ib[p], u, d.T, S, smask, s_last, ctl);
         const float4 c = ctl[k];
         X[p] += (int32_t)c.x;
         Y[p] += (int32_t)c.y;
@@ -454,18 +467,19 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
 // a launch compiled with SHIFT also carries the unshifted body and takes it,
 // uniformly per tile, for humans that do not need the shift, so that their
 // draws are the same bits whichever humans share the launch.
-template <int KT, int P, bool SHIFT, bool MS>
+template <int KT, int P, bool SHIFT, bool MS, int L = 1>
 __device__ __forceinline__ void rollout_tile(const RolloutDesc& d, int64_t first, uint32_t seed_lo,
                                              uint32_t seed_hi, TileShared& sh, uint32_t* win,
                                              int cap, float4* ctl) {
+  static_assert(L == 1 || (MS && !SHIFT), "the wide draw has no shifted form");
   if constexpr (SHIFT) {
     if (!d.shift) {
-      rollout_tile_body<KT, P, false, MS, false>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
+      rollout_tile_body<KT, P, false, MS, false, 1>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
       return;
     }
   }
   constexpr bool kPair = !SHIFT && !MS && KT > 0 && KT <= 16 && P % 2 == 0;
-  rollout_tile_body<KT, P, SHIFT, MS, kPair>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
+  rollout_tile_body<KT, P, SHIFT, MS, kPair, L>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
 }
 
 }  // namespace capred
