@@ -38,41 +38,59 @@ struct TileShared {
   float ibeta[CAP_MAX_B];
   uint32_t off[2];          // off-grid counters of the two in-flight steps
   uint32_t ntouch[3];       // first-touched window words per step (rotating)
+  int box[2][4];            // the tile's bounds: min x, min y, max x, max y (alternating)
   int last_pos;
 };
 
 __device__ __forceinline__ int64_t floor_shift16(int64_t v) { return v >> kLatticeShift; }
 
-// Histogram window of step t: every particle is within t * (Rx, Ry) lattice
-// units of the start, so its cell lies in [floor((X0 - tRx)/2^16),
-// floor((X0 + tRx)/2^16)] (clipped to the grid).  Uniform across the block.
+// Histogram window of a step: every particle was within [lx, hx] x [ly, hy]
+// (lattice units) k steps ago, so its cell lies in [floor((lx - k Rx)/2^16),
+// floor((hx + k Rx)/2^16)] (clipped to the grid).  Uniform across the block.
 struct Window {
   int x0, y0, w, h;
 };
 
-// Reach window of step t for a start (X0, Y0) on the lattice.
-__device__ __forceinline__ Window step_window_of(int32_t X0, int32_t Y0, int32_t Rx, int32_t Ry,
-                                                 int nx, int ny, int t) {
-  // 64-bit only for the reach t * R (up to 2^36); the shifted bounds fit 32 bits,
+__device__ __forceinline__ Window step_window_of(int32_t lx, int32_t ly, int32_t hx, int32_t hy,
+                                                 int32_t Rx, int32_t Ry, int nx, int ny, int k) {
+  // 64-bit only for the reach k * R (up to 2^36); the shifted bounds fit 32 bits,
   // so the clamps stay in scalar 32-bit arithmetic
-  const int64_t rx = (int64_t)t * Rx, ry = (int64_t)t * Ry;
-  int lx = (int)floor_shift16((int64_t)X0 - rx), hx = (int)floor_shift16((int64_t)X0 + rx);
-  int ly = (int)floor_shift16((int64_t)Y0 - ry), hy = (int)floor_shift16((int64_t)Y0 + ry);
-  lx = max(lx, 0);
-  ly = max(ly, 0);
-  hx = min(hx, nx - 1);
-  hy = min(hy, ny - 1);
+  const int64_t rx = (int64_t)k * Rx, ry = (int64_t)k * Ry;
+  int x0 = (int)floor_shift16((int64_t)lx - rx), x1 = (int)floor_shift16((int64_t)hx + rx);
+  int y0 = (int)floor_shift16((int64_t)ly - ry), y1 = (int)floor_shift16((int64_t)hy + ry);
+  x0 = max(x0, 0);
+  y0 = max(y0, 0);
+  x1 = min(x1, nx - 1);
+  y1 = min(y1, ny - 1);
   Window win;
-  win.x0 = lx;
-  win.y0 = ly;
-  win.w = hx >= lx ? hx - lx + 1 : 0;
-  win.h = hy >= ly ? hy - ly + 1 : 0;
+  win.x0 = x0;
+  win.y0 = y0;
+  win.w = x1 >= x0 ? x1 - x0 + 1 : 0;
+  win.h = y1 >= y0 ? y1 - y0 + 1 : 0;
   return win;
 }
 
+// LDS words of a window: two 16-bit counters per word (a tile never holds 65536
+// particles), rows padded to an even number of cells.
+__device__ __forceinline__ int window_words(const Window& w) { return ((w.w + 1) >> 1) * w.h; }
+
+// Reach window of step t for a start (X0, Y0) on the lattice.
 __device__ __forceinline__ Window step_window_at(const RolloutDesc& d, int32_t X0, int32_t Y0,
                                                  int t) {
-  return step_window_of(X0, Y0, d.Rx, d.Ry, d.nx, d.ny, t);
+  return step_window_of(X0, Y0, X0, Y0, d.Rx, d.Ry, d.nx, d.ny, t);
+}
+
+// Least v of the wave's lanes, in lane 63.
+__device__ __forceinline__ int wave_min63(int v) {
+#define CAP_MIN_DPP(ctrl) v = min(v, __builtin_amdgcn_update_dpp(v, v, ctrl, 0xF, 0xF, false))
+  CAP_MIN_DPP(0x111);   // row_shr 1, 2, 4, 8, then the rows below
+  CAP_MIN_DPP(0x112);
+  CAP_MIN_DPP(0x114);
+  CAP_MIN_DPP(0x118);
+  CAP_MIN_DPP(0x142);
+  CAP_MIN_DPP(0x143);
+#undef CAP_MIN_DPP
+  return v;
 }
 
 __device__ __forceinline__ uint32_t pick_word(const uint4& w, int s) {
@@ -156,6 +174,16 @@ __device__ __forceinline__ void sort_by_pair(int64_t first, int tile_n, int J, u
 // list entry) take both buffers and wait at one more barrier for the previous
 // flush; larger windows bin with global atomics.
 //
+// A step's window is what the particles can have reached since their bounds were
+// last known: the start's at first, and from the step on whose window would
+// outgrow a buffer, the tile's true bounds, taken anew every fourth step while
+// that is so (four wave reductions and a barrier).  A cloud spans a fraction of
+// its reach (the 64-human scene at step 200: 6500 words of 29000), so that steps
+// which went to global atomics one particle at a time, at the 2.7e10 a second
+// that the device takes, stay in LDS: 16 humans x 10^5 particles x 100 steps of
+// 2.4 cells on 256 x 256 cells, a cycle of 4.21 ms before and 2.42 after; eight
+// humans of the 64-human scene 16.2 -> 15.9 ms.
+//
 // MS (several speeds): draw_control over the S K controls; `ctl` is an LDS
 // array of CAP_MAX_U float4 that receives (fx, fy, s2) of every control, read
 // per lane for the block recomputation and the step (unused otherwise).
@@ -203,6 +231,7 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
     sh.off[1] = 0u;
     sh.ntouch[0] = sh.ntouch[1] = sh.ntouch[2] = 0u;
   }
+  if (tid < 8) sh.box[tid >> 2][tid & 3] = INT_MAX;
   __syncthreads();
 
   // ---- per-particle (beta, g) draw, held for the whole horizon
@@ -260,7 +289,7 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   // The descriptor's fields that every step reads, in scalar registers for the
   // whole tile: it lies in memory that the loop's stores could alias, so each
   // use would be a load and a wait.
-  const int H = d.H, nx = d.nx, ny = d.ny, X0 = d.X0, Y0 = d.Y0, Rx = d.Rx, Ry = d.Ry;
+  const int H = d.H, nx = d.nx, ny = d.ny, Rx = d.Rx, Ry = d.Ry;
   const uint32_t human = d.human;
   uint32_t* const counts = d.counts;
   uint8_t* const trace_k = d.trace_k;
@@ -271,6 +300,8 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   uint4 rw[P];
   const int list_cap = P * nthr;
   int m3 = 1;  // t mod 3
+  // after step t_box the particles lie in [lox, hix] x [loy, hiy]
+  int lox = d.X0, loy = d.Y0, hix = lox, hiy = loy, t_box = 0, box_buf = 0;
   for (int t = 1; t <= H; ++t, m3 = (m3 == 2 ? 0 : m3 + 1)) {
     const int s = (t - 1) & 3;
     if (s == 0) {
@@ -283,12 +314,39 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
 #pragma unroll
       for (int p = 0; p < P; ++p)
         rw[p] = philox10(idx[p], (uint32_t)((t - 1) >> 2), human, c3_head, klo, khi);
+      // The windows outgrow the buffer within these four steps: take the
+      // particles' true bounds.
+      if (t > 1 && window_words(step_window_of(lox, loy, hix, hiy, Rx, Ry, nx, ny,
+                                               min(t + 3, H) - t_box)) > cap) {
+        int b[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+          if (act[p]) {
+            b[0] = min(b[0], X[p]);
+            b[1] = min(b[1], Y[p]);
+            b[2] = min(b[2], ~X[p]);
+            b[3] = min(b[3], ~Y[p]);
+          }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          b[i] = wave_min63(b[i]);
+          if ((tid & 63) == 63) atomicMin(&sh.box[box_buf][i], b[i]);
+        }
+        __syncthreads();
+        lox = __builtin_amdgcn_readfirstlane(sh.box[box_buf][0]);
+        loy = __builtin_amdgcn_readfirstlane(sh.box[box_buf][1]);
+        hix = ~__builtin_amdgcn_readfirstlane(sh.box[box_buf][2]);
+        hiy = ~__builtin_amdgcn_readfirstlane(sh.box[box_buf][3]);
+        t_box = t - 1;
+        // the other one was read before an earlier step's barrier and is next
+        // taken after a later one's
+        box_buf ^= 1;
+        if (tid < 4) sh.box[box_buf][tid] = INT_MAX;
+      }
     }
-    const Window wd = step_window_of(X0, Y0, Rx, Ry, nx, ny, t);
-    // two 16-bit counters per LDS word (a tile never holds 65536 particles);
-    // rows padded to an even number of cells
+    const Window wd = step_window_of(lox, loy, hix, hiy, Rx, Ry, nx, ny, t - t_box);
     const int half_w = (wd.w + 1) >> 1;
-    const int words = half_w * wd.h;
+    const int words = window_words(wd);
     const bool single = words > cap && words <= 2 * cap && words <= 65536;
     const bool lds_mode = words <= cap || single;
     uint32_t* buf = single ? win : win + (t & 1) * cap;
