@@ -116,10 +116,10 @@ __host__ __device__ constexpr size_t window_lds_bytes(int cap, int particles_per
 constexpr int kSortSteps = 24;
 
 template <int P>
-__device__ __forceinline__ void sort_by_pair(int64_t first, int tile_n, int J, uint32_t* hist,
-                                             uint16_t* lists, uint32_t* idx, int* pair,
-                                             bool* act) {
-  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+__device__ __forceinline__ void sort_by_pair(int tid, int64_t first, int tile_n, int J,
+                                             uint32_t* hist, uint16_t* lists, uint32_t* idx,
+                                             int* pair, bool* act) {
+  const int nthr = blockDim.x, lane = tid & 63;
   __syncthreads();   // hist may lie where the pair CDF was read
   for (int j = tid; j <= J; j += nthr) hist[j] = 0u;
   __syncthreads();
@@ -200,7 +200,12 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
                                                   uint32_t seed_lo, uint32_t seed_hi,
                                                   TileShared& sh, uint32_t* win, int cap,
                                                   float4* ctl) {
-  const int tid = threadIdx.x;
+  // Opaque, so that a persistent block derives its lanes' addresses anew in each
+  // tile: kept across the tiles they took the registers of the tile's own values
+  // and spilled to scratch (38 registers at K = 16, P = 4), and a launch with
+  // scratch starts later: the 16-human cycle 0.927 ms with, 0.905 without.
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int nthr = blockDim.x;
   const int J = d.G * d.B;
   // ---- shared tables
@@ -263,7 +268,8 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   }
   uint16_t* lists = reinterpret_cast<uint16_t*>(win + 2 * cap);
   if (kFar && d.H >= kSortSteps)
-    sort_by_pair<P>(first, tile_n, J, reinterpret_cast<uint32_t*>(sh.P), lists, idx, pair, act);
+    sort_by_pair<P>(tid, first, tile_n, J, reinterpret_cast<uint32_t*>(sh.P), lists, idx, pair,
+                    act);
   int32_t X[P], Y[P], GXp[P], GYp[P];
   float ib[P], nbs[P];
 #pragma unroll
