@@ -271,7 +271,7 @@ typedef struct cap_plan_config {
   int32_t max_obs;              /* new observed positions per slot per cycle, 1..8 */
   int32_t ring;                 /* per-cycle buffer ring depth, 1..4            */
   int32_t block_threads;        /* 0 = default; else 256, 512 or 1024           */
-  int32_t particles_per_thread; /* 0 = default; else 1, 2 or 4                  */
+  int32_t particles_per_thread; /* 0 = default (per-human launches: 1); else 1, 2 or 4 */
   int32_t lds_bytes;            /* 0 = default; LDS histogram window per block  */
   int32_t grid_blocks;          /* 0 = default: fill every CU at each rollout
                                    variant's occupancy; else persistent blocks */
@@ -345,11 +345,11 @@ cap_status cap_plan_run(cap_plan* plan, uint64_t seed, uint32_t cycle, void* str
 cap_status cap_plan_replay_rollout(cap_plan* plan, void* stream, void* ev_start, void* ev_end);
 /* Block the host until the last run has completed on the device. */
 cap_status cap_plan_sync(cap_plan* plan);
-/* Totals over the active slots: particles, particle-steps, and tiles of
- * particles_per_thread * block_threads particles (the per-human launches'
- * tiles; the persistent launch cuts the same particles into tiles of that
- * size, half of it and a quarter of it, sized per cycle to the resident
- * blocks). */
+/* Totals over the active slots: particles, particle-steps, and the per-human
+ * launches' tiles of block_threads * the configured particles_per_thread (1 if
+ * that was 0) particles (the persistent launch cuts the same particles into
+ * tiles of particles_per_thread * block_threads, half of it and a quarter of
+ * it, sized per cycle to the resident blocks). */
 cap_status cap_plan_stats(const cap_plan* plan, int64_t* particles, int64_t* particle_steps,
                           int32_t* tiles);
 /* Union stage (Sec. IV-B: the planner reads one occupancy map of all humans):

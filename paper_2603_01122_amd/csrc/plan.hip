@@ -423,6 +423,9 @@ constexpr int kVariants = 3, kWideVariant = 2, kWideLanes = 4;
 // additions for nothing.  Five humans of 8192 particles x 6 steps, 96 controls:
 // rollout 92 -> 49 us.
 constexpr int64_t kWideParticles = 65536;
+// LDS windows of a plan whose caller leaves them open: with the whole shape open,
+// and otherwise (see cap_plan_create).
+constexpr int kOpenLds = 128 * 1024, kPlainLds = 40 * 1024;
 
 struct Entry {
   uint32_t* queues = nullptr;   // this entry's tile counters and update tickets (device)
@@ -445,10 +448,12 @@ struct cap_plan {
   uint32_t* queues = nullptr;   // tile counters and update tickets of every ring entry (device)
   size_t entry_bytes = 0;
   int cap_words = 0;            // LDS window words per buffer
+  int plain_words = 0;          // the same, of the per-human launches
   int grid_blocks[capred::kVariants] = {};  // persistent blocks per launch, per rollout variant
   int n_cus = 1;                // compute units of the device
   int smooth_blocks = 0;        // persistent blocks of the smoothing stage (0: no stage)
-  int per_tile = 0;
+  int per_tile = 0;             // particles of a per-human launch's tile
+  size_t lds = 0;               // dynamic LDS of the persistent launch
   const void* rollout_fn[capred::kVariants] = {};              // [rollout variant] (wide: may be null)
   const void* rollout_one_fn[2] = {nullptr, nullptr};
   int last_variant = 0;
@@ -518,7 +523,7 @@ static cap_status launch_rollout(cap_plan* p, const Entry& e, int variant, hipSt
   uint32_t* q = e.queues;
   void* args[] = {(void*)&base, (void*)&q, (void*)&p->cap_words};
   CAP_HIP(hipLaunchKernel(p->rollout_fn[variant], dim3(p->grid_blocks[variant]), dim3(p->cfg.block_threads), args,
-                          window_lds_bytes(p->cap_words, p->per_tile), s));
+                          p->lds, s));
   return CAP_OK;
 }
 
@@ -639,6 +644,14 @@ static void split_tiles(const int32_t* units, int n, int P, int R, int C,
       }
     }
   }
+  // Still short of quarters: the humans' odd halves would be the largest tiles (four
+  // humans of 30 units each on 256 CUs: 285 us with them, 205 without).
+  if (P >= 4)
+    for (int i = n - 1; i >= 0 && need_quarter > 0; --i)
+      for (; cnt[i][1] > 0 && need_quarter > 0 && need_half < 0; ++need_half, need_quarter -= 2) {
+        --cnt[i][1];
+        cnt[i][2] += 2;
+      }
 }
 
 // Blocks that share one human's belief update: one while a block's Deltas (at
@@ -804,6 +817,22 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
   if (cfg.max_obs < 1 || cfg.max_obs > kMaxObs) return fail(CAP_E_INVALID, "max_obs must be in [1, 8]");
   if (cfg.ring == 0) cfg.ring = 2;
   if (cfg.ring < 1 || cfg.ring > 4) return fail(CAP_E_INVALID, "ring must be in [1, 4]");
+  // Launch shape when the caller leaves it open: blocks of 1024 threads, which are
+  // alone on their CU at more than 64 registers and may have its LDS, with four
+  // particles a thread (several speeds: two), as larger tiles add each touched
+  // cell less often; the tile cut makes smaller ones where a cycle has few.
+  // Against one particle a thread and 40 KiB, K = 16, 50 steps: 64 humans x 50000
+  // 2.70 -> 1.66 ms, 16 x 10^5 (100 steps) 2.41 -> 1.88, 4 x 30000 208 -> 205 us,
+  // 2 x 2000 (10 steps) 65 -> 66 us; two speeds, 16 x 30000: 0.88 -> 0.72 ms.  The
+  // per-human launches, which are not cut, keep one.
+  const bool open_shape = cfg.block_threads == 0 && cfg.particles_per_thread == 0 &&
+                          cfg.lds_bytes <= kOpenLds;
+  const int plain_p = cfg.particles_per_thread == 0 ? 1 : cfg.particles_per_thread;
+  const int plain_lds = cfg.lds_bytes == 0 ? kPlainLds : cfg.lds_bytes;
+  if (open_shape) {
+    cfg.particles_per_thread = pc.S == 1 ? 4 : 2;
+    if (cfg.lds_bytes == 0) cfg.lds_bytes = kOpenLds;
+  }
   if (cfg.block_threads == 0) cfg.block_threads = 1024;
   if (cfg.block_threads != 256 && cfg.block_threads != 512 && cfg.block_threads != 1024)
     return fail(CAP_E_INVALID, "block_threads must be 256, 512 or 1024");
@@ -811,7 +840,7 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
   if (cfg.particles_per_thread != 1 && cfg.particles_per_thread != 2 &&
       cfg.particles_per_thread != 4)
     return fail(CAP_E_INVALID, "particles_per_thread must be 1, 2 or 4");
-  if (cfg.lds_bytes == 0) cfg.lds_bytes = 40 * 1024;
+  if (cfg.lds_bytes == 0) cfg.lds_bytes = kPlainLds;
   if (cfg.lds_bytes < 2048 || cfg.lds_bytes > 144 * 1024)
     return fail(CAP_E_INVALID, "lds_bytes must be in [2 KiB, 144 KiB]");
   if (cfg.max_smooth_radius < 0 || cfg.max_smooth_radius > kMaxSmoothRadius)
@@ -820,10 +849,16 @@ extern "C" cap_status cap_plan_create(const cap_plan_config* cfg_in, cap_plan** 
   p->cfg = cfg;
   p->slots.resize(cfg.n_slots);
   p->ring.resize(cfg.ring);
-  p->per_tile = cfg.block_threads * cfg.particles_per_thread;
+  p->per_tile = cfg.block_threads * plain_p;
   p->cap_words = cfg.lds_bytes / (2 * (int)sizeof(uint32_t));
-  select_kernels(cfg.K, pc.S, cfg.particles_per_thread, p->rollout_fn, p->rollout_one_fn);
-  const size_t dyn = window_lds_bytes(p->cap_words, p->per_tile);
+  p->plain_words = plain_lds / (2 * (int)sizeof(uint32_t));
+  {
+    const void* other[kVariants] = {};
+    select_kernels(cfg.K, pc.S, cfg.particles_per_thread, p->rollout_fn, other);
+    select_kernels(cfg.K, pc.S, plain_p, other, p->rollout_one_fn);
+  }
+  p->lds = window_lds_bytes(p->cap_words, cfg.block_threads * cfg.particles_per_thread);
+  const size_t dyn = p->lds;
   hipError_t e = hipSuccess;
   for (int v = 0; v < kVariants; ++v) {
     if (!p->rollout_fn[v]) continue;
@@ -1077,9 +1112,9 @@ extern "C" cap_status cap_plan_run_plain(cap_plan* p, uint64_t seed, uint32_t cy
     hipLaunchKernelGGL(plan_zero_kernel, dim3(zb), dim3(256), 0, s, base, en.queues, i);
     const int tiles = H->tile_begin[i + 1] - H->tile_begin[i];
     int si = i;
-    void* args[] = {(void*)&base, (void*)&si, (void*)&p->cap_words};
+    void* args[] = {(void*)&base, (void*)&si, (void*)&p->plain_words};
     CAP_HIP(hipLaunchKernel(p->rollout_one_fn[sl[i].rd.shift ? 1 : 0], dim3(tiles), dim3(p->cfg.block_threads), args,
-                            window_lds_bytes(p->cap_words, p->per_tile), s));
+                            window_lds_bytes(p->plain_words, p->per_tile), s));
     if (sl[i].probs && sl[i].smooth_r == 0) {
       const unsigned nb = (unsigned)std::min(4 * sl[i].rd.H, 4096);
       hipLaunchKernelGGL(plan_normalize_kernel, dim3(nb), dim3(256), 0, s, base, i);
