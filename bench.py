@@ -40,16 +40,15 @@ def log(msg):
 
 
 def algorithmic_ops(K: int, r: dict) -> float:
-    """Minimal VALU time per particle-step of the stable-form rollout, in
-    full-rate lane-operation slots (one FP32 FMA = 1; rates r from the probes).
-    Operation counts of the algorithm:
-      per heading: dot product shared by the two opposite headings (1),
-                   n_k = |s|^2 +- dot (1), |a|^2 + n_k (1), scaled
-                   denominator FMA (1), exponent multiply (1), prefix add (1)
-                   = 6 full-rate, plus sqrt, reciprocal and exp2;
+    """Minimal VALU time per particle-step of the rollout, in full-rate
+    lane-operation slots (one FP32 FMA = 1; rates r from the probes).  Operation
+    counts of the draw of a particle some steps away from its goal (K = 8, 16, 32;
+    nearly all draws):
+      features:    three harmonics of the heading angle, tolerance = 18;
+      per heading: exponent (9 for four headings), prefix add (1), exp2;
       inverse CDF: binary search, log2(K) compare + select pairs;
-      per step:    offset/convert/|a|^2/|a| scale/2a/uniform/threshold/step/
-                   cell/bounds = 22 full-rate plus one sqrt;
+      per step:    offset/convert/|a|^2/uniform/threshold/step/cell/bounds = 22
+                   full-rate plus one reciprocal square root;
       Philox:      one 10-round block per 4 steps = 5 wide multiplies and
                    10 full-rate ops per step.
     Transcendentals issue in one slot and then occupy their own pipe for
@@ -62,9 +61,9 @@ def algorithmic_ops(K: int, r: dict) -> float:
 
 def algorithmic_slots(K: int, r: dict):
     """(issue slots, transcendental-pipe slots) per particle-step; see algorithmic_ops."""
-    trans = K * 3 + 1
-    issue = K * 6 + 2 * math.log2(K) + 22 + 10 + trans + 5 * r["mul64"]
-    pipe = K * (r["sqrt"] + r["rcp"] + r["exp2"]) + r["sqrt"]
+    trans = K + 1
+    issue = K * 3.25 + 18 + 2 * math.log2(K) + 22 + 10 + trans + 5 * r["mul64"]
+    pipe = K * r["exp2"] + r["sqrt"]
     return issue, pipe
 
 
