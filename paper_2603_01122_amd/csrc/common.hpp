@@ -290,9 +290,9 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
 // back: 2e-4 at K = 16 and small |nb s|.
 //
 // Bound by VALU issue as before, with fewer slots: 120 instructions a draw
-// instead of 170 at K = 16 (17 transcendental instead of 49, two slots each), 182
-// instead of 220 a particle-step with everything else.  A lone cycle of the
-// 16-human workload takes 0.99 ms instead of 1.24, one of 64 humans x 2^20
+// instead of 170 at K = 16 (17 transcendental instead of 49, two slots each), 174
+// instead of 219 a particle-step with everything else.  A cycle of the
+// 16-human workload takes 0.91 ms instead of 1.18, one of 64 humans x 2^20
 // particles (K = 32) 125 ms instead of 178 (each at its best launch shape).
 struct FarConst {
   float d2;       // smallest |a|^2 (lattice units) the filter takes; inf: none
