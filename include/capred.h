@@ -300,7 +300,11 @@ typedef struct cap_slot_desc {
   int32_t reset_belief;         /* 1: write the uniform prior before the first update */
   int32_t smooth_radius;        /* 0: probs = count / N; 1..max_smooth_radius: probs
                                    are the Gaussian-smoothed occupancy of
-                                   cap_smooth_occupancy (requires probs_dev)       */
+                                   cap_smooth_occupancy (requires probs_dev), every
+                                   cell written each cycle; with 0 a cycle writes
+                                   the cells that this or the entry's previous
+                                   cycle can have reached (all cells on the first
+                                   one), and the rest stay as they are             */
   double smooth_sigma;          /* kernel width in cells, > 0 when smooth_radius > 0 */
   uint32_t speed_mask;          /* allowed speeds of the prediction (bit s; 0 = all) */
 } cap_slot_desc;

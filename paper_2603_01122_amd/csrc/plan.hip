@@ -255,9 +255,10 @@ __global__ void __launch_bounds__(256)
 
 // Smoothing tiles (step, 32 rows x 64 columns) of every slot that asks for
 // Gaussian-smoothed probabilities, as one index space (smooth_begin prefix)
-// walked by a persistent grid.  A tile farther than the radius from the step's
-// clear region is skipped: its counts are zero, and its probabilities are
-// still the zeros of an earlier cycle (see clear_region).
+// walked by a persistent grid.  Every cell is written each cycle, whatever the
+// caller did to the grid in between.  A tile farther than the radius from the
+// step's clear region takes zeros without a look at its counts, which are zero
+// there (see clear_region).
 __global__ void __launch_bounds__(kSmoothThreads)
     plan_smooth_kernel(const uint8_t* __restrict__ base, int only) {
   extern __shared__ __align__(16) float tile[];
@@ -284,15 +285,20 @@ __global__ void __launch_bounds__(kSmoothThreads)
     const int by = rem / tx, bx = rem - by * tx;
     const int y0 = by * kBandRows, x0 = bx * kBandCols;
     const Window reg = clear_region(sd, t + 1);
-    if (reg.w == 0 || reg.h == 0 || x0 >= reg.x0 + reg.w + r || x0 + kBandCols <= reg.x0 - r ||
-        y0 >= reg.y0 + reg.h + r || y0 + kBandRows <= reg.y0 - r)
-      continue;
     const size_t plane = (size_t)ny * nx;
+    float* o = sd.probs + (size_t)t * plane;
+    if (reg.w == 0 || reg.h == 0 || x0 >= reg.x0 + reg.w + r || x0 + kBandCols <= reg.x0 - r ||
+        y0 >= reg.y0 + reg.h + r || y0 + kBandRows <= reg.y0 - r) {
+      const int x = x0 + (int)(threadIdx.x & 63u), y1 = min(y0 + kBandRows, ny);
+      if (x < nx)
+        for (int y = y0 + (int)(threadIdx.x >> 6); y < y1; y += kSmoothThreads / 64)
+          as_global(o)[(size_t)y * nx + x] = 0.f;
+      continue;
+    }
     float* un = sd.in_union && t + 1 <= H->union_H
                     ? H->union_out + (size_t)t * H->union_nx * H->union_ny
                     : nullptr;
     const uint32_t* c = sd.rd.counts + (size_t)t * plane;
-    float* o = sd.probs + (size_t)t * plane;
     const float Nf = (float)sd.rd.N;
     const float* w = sd.smooth_w.w;
     switch (smooth_bucket(r)) {
