@@ -16,9 +16,10 @@ constexpr int kMaxChunkT = 64;     // transitions per chunk
 template <int NT>
 struct BeliefShared {
   static constexpr int kDeltas = 4 * NT;
+  static constexpr int kTerms = NT > CAP_MAX_J ? NT : CAP_MAX_J;
   BeliefModel m;           // staged: lanes read its tables by their own index
   double dl[kDeltas];      // Delta of a chunk of transitions x goals x controls
-  double part[CAP_MAX_J];  // sums of the (pair, share of the transitions) tasks
+  double term[kTerms];     // policy terms of the chunk, [transition][pair]
   int ks[kMaxChunkT];
 };
 
@@ -52,7 +53,7 @@ __device__ __forceinline__ int recover_control(const BeliefModel& m, float dx, f
 // log pi(u* | z; beta_b, g) for every b over the U controls in plain FP32 (the
 // trajectory log-likelihood's terms: its bar is relative to |LL|, a sum of
 // hundreds of terms, so FP32 logits meet it; the posterior update uses the
-// compensated policy_delta and policy_term_from below).
+// compensated policy_delta and policy_term_lanes below).
 // Delta_u = |a + s_u| - |a| with a = z - g carried as an unevaluated sum
 // (hi + lo, exact subtraction), from the cancellation-free quotient
 // (2 a.s_u + |s_u|^2) / (|a + s_u| + |a|); then l_u = -beta Delta_u and
@@ -224,16 +225,19 @@ __device__ __forceinline__ double policy_term_lanes(const double* dl, int U, int
 
 // Adds sum_t ell_t(g, b) of the goals [g0, g1) and betas [b0, b1) to
 // log_belief (not yet normalised).  Every Delta of a chunk of transitions x
-// goals x controls is evaluated once, in parallel, into LDS; then groups of L
-// lanes take the tasks (pair, share of the transitions), one policy term at a
-// time.  What bounds it is the latency of dependent FP64 work, so every level
-// (transitions, goals, pairs, controls) is spread over the lanes: with one
-// thread per pair running its controls' exponentials one after another and the
-// transitions in series, 40 observations of a 96-control model over 21 goals x
-// 5 betas took 2524 us.  Each sum runs in a fixed order for given sizes and
-// block size (bitwise reproducible).  Now 13.0 us for that history (one block
-// per pair) and 8.4 us for 10 observations of 8 controls over 2 goals x 4
-// betas (38.7 us before), most of it the round trips and chains of one term.
+// goals x controls is evaluated once, in parallel, into LDS; groups of L lanes
+// then take the policy terms of the chunk's (transition, pair)s one at a time,
+// and one thread per pair adds that pair's terms in transition order.  So a
+// pair's sum does not depend on the chunks, the block size or the share of the
+// pairs that the block has: the single-human call, a plan's shared update and
+// its per-human form give the same bits.  What bounds it is the latency of
+// dependent FP64 work, so every level (transitions, goals, pairs, controls) is
+// spread over the lanes: with one thread per pair running its controls'
+// exponentials one after another and the transitions in series, 40 observations
+// of a 96-control model over 21 goals x 5 betas took 2524 us.  Now 13.0 us for
+// that history (one block per pair) and 8.4 us for 10 observations of 8 controls
+// over 2 goals x 4 betas (38.7 us before), most of it the round trips and chains
+// of one term.
 template <int NT, int L>
 __device__ __forceinline__ void belief_terms(const float* __restrict__ obs,
                                              int n_obs, double* log_belief, int g0,
@@ -242,14 +246,15 @@ __device__ __forceinline__ void belief_terms(const float* __restrict__ obs,
   const int tid = threadIdx.x;
   const int B = m.B, U = m.U, nb = b1 - b0;
   constexpr int kGroups = NT / L;
+  constexpr int kPer = (CAP_MAX_J + NT - 1) / NT;   // pairs of a thread
   const int grp = tid / L, sub = tid % L;
   const int gstep = max(1, min(g1 - g0, sh.kDeltas / U));
   for (int gb = g0; gb < g1; gb += gstep) {
-    const int gn = min(gstep, g1 - gb), pairs = gn * nb;
-    const int tstep = min(kMaxChunkT, sh.kDeltas / (gn * U));
-    const int shares = max(1, min(min(n_obs, tstep), kGroups / pairs));
-    const int tasks = pairs * shares;   // at most max(pairs, kGroups) <= CAP_MAX_J
-    for (int k = tid; k < tasks; k += NT) sh.part[k] = 0.0;
+    const int gn = min(gstep, g1 - gb), pairs = gn * nb;   // pairs <= CAP_MAX_J <= kTerms
+    const int tstep = min(kMaxChunkT, min(sh.kDeltas / (gn * U), sh.kTerms / pairs));
+    double sum[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) sum[r] = 0.0;
     for (int t0 = 0; t0 < n_obs; t0 += tstep) {
       const int tn = min(tstep, n_obs - t0);
       for (int i = tid; i < tn; i += NT) {
@@ -264,27 +269,32 @@ __device__ __forceinline__ void belief_terms(const float* __restrict__ obs,
         sh.dl[item] = policy_delta(o, m.sx[u], m.sy[u]);
       }
       __syncthreads();
-      for (int k = grp; k < tasks; k += kGroups) {
-        const int q = k / pairs, p = k - q * pairs, gl = p / nb;
+      for (int k = grp; k < tn * pairs; k += kGroups) {
+        const int tl = k / pairs, p = k - tl * pairs, gl = p / nb;
         const double beta = (double)m.beta[b0 + p - gl * nb];
-        double acc = 0.0;
-        for (int tl = q; tl < tn; tl += shares) {
-          const int ks = sh.ks[tl];
-          if (ks >= 0)   // below 1e-9 m: no information
-            acc += policy_term_lanes<L>(sh.dl + (tl * gn + gl) * U, U, ks, beta, sub);
-        }
-        if (sub == 0) sh.part[k] += acc;
+        const int ks = sh.ks[tl];
+        double ell = 0.0;   // below 1e-9 m: no information
+        if (ks >= 0) ell = policy_term_lanes<L>(sh.dl + (tl * gn + gl) * U, U, ks, beta, sub);
+        if (sub == 0) sh.term[k] = ell;
       }
       __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const int p = tid + r * NT;
+        if (p < pairs) {
+#pragma unroll 8
+          for (int tl = 0; tl < tn; ++tl) sum[r] += sh.term[tl * pairs + p];
+        }
+      }
+      // (the next chunk's terms come after another barrier)
     }
-    for (int p = tid; p < pairs; p += NT) {
-      const int gl = p / nb, j = (gb + gl) * B + b0 + p - gl * nb;
-      double s = 0.0;
-      for (int q = 0; q < shares; ++q) s += sh.part[q * pairs + p];
-      log_belief[j] += s;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int p = tid + r * NT, gl = p / nb;
+      if (p < pairs) log_belief[(gb + gl) * B + b0 + p - gl * nb] += sum[r];
     }
-    __syncthreads();
   }
+  __syncthreads();
 }
 
 template <int NT>
