@@ -10,11 +10,13 @@
 // a step -- FP64 sine and cosine, the grid read, the cost -- needs no other
 // step's.  So the waves stage the controls, two waves run the sums of v and
 // theta through LDS, all waves take their steps' sine and cosine, two waves run
-// x and y, and all waves add their steps' costs (perturbations laid out
-// [T][N][2]: a wave reads 64 consecutive (a, omega) pairs per step).  The robot
-// state and the cost run in FP64: the collision term is a step function of the
-// grid cell, and FP64 positions (every product and sum rounded on its own)
-// keep the cell decisions of this kernel and of an FP64 reference identical
+// x and y, all waves take their steps' costs, and one wave adds those in step
+// order, so that a sample's cost depends neither on the batch nor on the waves
+// (perturbations laid out [T][N][2]: a wave reads 64 consecutive (a, omega) pairs
+// per step).  The robot state and the cost run in FP64: the collision term is a
+// step function of the grid cell, and FP64 positions (every product and sum
+// rounded on its own) keep the cell decisions of this kernel and of an FP64
+// reference identical
 // except within ~1e-12 m of a cell edge.  The update runs one block per step
 // t; every block recomputes min S and the weight sum with the same fixed-order
 // reduction, so the result does not depend on the launch.
@@ -47,15 +49,15 @@ __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) 
 #pragma clang fp contract(off)
   constexpr int kOwn = kChunkSteps / W;   // steps of a wave per chunk
   static_assert(kChunkSteps % W == 0 && W >= 2, "a chunk is whole steps per wave");
+  static_assert(kChunkSteps % 16 == 0, "the costs are summed 16 steps at a time");
   // row t + 1 belongs to step t of the chunk, row 0 to the state before it
   __shared__ double A[kChunkSteps + 1][64], B[kChunkSteps + 1][64];
-  __shared__ double part[W][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
   const int is = min(i, a.N - 1);   // lanes past the end repeat the last sample
   const double2* dl = reinterpret_cast<const double2*>(a.delta);
   const size_t plane = (size_t)a.nx * a.ny;
-  double s = 0.0;
+  double sum = 0.0;   // wave 0: the sample's cost so far
   double c0 = wave == 0 ? a.z0[2] : a.z0[3];   // wave 0 carries v and x, wave 1 theta and y
   double c1 = wave == 0 ? a.z0[0] : a.z0[1];
   for (int t0 = 0; t0 < a.T; t0 += kChunkSteps) {
@@ -124,11 +126,12 @@ __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) 
         y[k] = B[t + 1][lane];
       }
     }
-    __syncthreads();   // the next chunk rewrites A and B
+    // (A from here on: each step's cost, in the row that its wave alone read)
 #pragma unroll
     for (int k = 0; k < kOwn; ++k) {
       const int t = t0 + wave + k * W + 1;   // 1 .. T
       if (wave + k * W < tn) {
+        double s = 0.0;
         const double e0 = x[k] - a.goal[0], e1 = y[k] - a.goal[1], e2 = v[k] - a.goal[2],
                      e3 = th[k] - a.goal[3];
         if (t < a.T) {
@@ -151,16 +154,25 @@ __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) 
           s += a.Qf[2] * e2 * e2;
           s += a.Qf[3] * e3 * e3;
         }
+        A[wave + k * W + 1][lane] = s;
+      } else {
+        A[wave + k * W + 1][lane] = 0.0;   // up to whole batches of the sum below
       }
     }
+    __syncthreads();
+    if (wave == 0) {
+      constexpr int kBatch = 16;   // reads in flight together
+      for (int t = 1; t <= tn; t += kBatch) {
+        double c[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) c[k] = A[t + k][lane];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) sum += c[k];
+      }
+    }
+    if (t0 + kChunkSteps < a.T) __syncthreads();   // the next chunk rewrites A and B
   }
-  part[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0 && i < a.N) {
-    double sum = part[0][lane];
-    for (int w = 1; w < W; ++w) sum += part[w][lane];
-    a.S[i] = sum;
-  }
+  if (wave == 0 && i < a.N) a.S[i] = sum;
 }
 
 // Block-wide reduction of M values in a fixed order (a butterfly in each wave,
@@ -200,16 +212,28 @@ __global__ void __launch_bounds__(kUpdateThreads)
   for (int i = threadIdx.x; i < N; i += kUpdateThreads) m = fmin(m, S[i]);
   block_fold<true, 1>(&m, red);
   double acc[3] = {0.0, 0.0, 0.0};   // sum w, sum w delta
-  const double rate = 1.0 / tau;
   const double2* dl = reinterpret_cast<const double2*>(delta) + (size_t)t * N;
+  // (m - S) / tau as a product with the rounded reciprocal and one correction,
+  // which rounds as the division does (Markstein); out of its range, and for
+  // exponents whose weight is 0, the division and the product themselves.
+  const double rate = 1.0 / tau;
+  const auto add = [&](auto quotient) {
 #pragma unroll 8
-  for (int i = threadIdx.x; i < N; i += kUpdateThreads) {
-    const double w = exp((m - S[i]) * rate);
-    const double2 d = dl[i];
-    acc[0] += w;
-    acc[1] += w * d.x;
-    acc[2] += w * d.y;
-  }
+    for (int i = threadIdx.x; i < N; i += kUpdateThreads) {
+      const double w = exp(quotient(m - S[i]));
+      const double2 d = dl[i];
+      acc[0] += w;
+      acc[1] += w * d.x;
+      acc[2] += w * d.y;
+    }
+  };
+  if (tau > 0x1p-500 && tau < 0x1p500)
+    add([&](double x) {
+      const double q = x * rate;
+      return q > -4096.0 ? fma(fma(-q, tau, x), rate, q) : q;
+    });
+  else
+    add([&](double x) { return x / tau; });
   block_fold<false, 3>(acc, red);
   if (threadIdx.x == 0) {
     U[2 * t] += acc[1] / acc[0];
