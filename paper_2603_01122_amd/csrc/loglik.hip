@@ -119,17 +119,19 @@ __global__ void __launch_bounds__(1024)
 // with yhat_k = (a + s_k)/d_k and, to avoid cancellation between unit vectors,
 //   yhat_k - yhat_* = a (Delta_* - Delta_k)/(d_k d_*) + s_k/d_k - s_*/d_*.
 //
-// KT > 0 (the model has KT headings, every loop over them unrolled): Delta is
-// taken relative to its minimum, so the logits need no shift and E[Delta] no
-// subtraction of two like sums.  Per beta the KT probabilities are formed, their
-// sum and first moment, and then added, times w beta / sum, into one coefficient
-// per heading; the unit vectors enter once, after the betas.  That is two FMAs
-// fewer per (beta, heading) than three moments per beta, and leaves three arrays
-// of KT registers live instead of four.  The per-lane sums of d log beta are
-// kept in LDS.  (KT = 32, 1024 tracks x 200 steps x 8 goals x 9 betas: 197 -> 148 us
-// at 128 registers, four waves per SIMD; 152 at 136 registers and three.)
+//
+// KT > 0 (the model has KT headings, every loop over them unrolled): the unit
+// vectors' differences are formed once per heading (from each distance's own
+// square root; the chosen heading's is exactly zero).  Per beta the KT
+// probabilities give four moments, which are added over betas and steps in
+// FP64; the per-lane sums of d log beta are kept in LDS.  Four arrays of KT
+// values live over the betas: at K = 32, 160 registers and three waves per SIMD,
+// so blocks of at most 768 threads (1024 tracks x 200 steps x 8 goals x 9 betas:
+// 149 us; at 128 registers, the differences of Delta formed anew for every beta,
+// 160).  One coefficient per heading in place of the two goal moments takes 135,
+// but adds the betas in FP32.
 template <int KT>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(KT > 16 ? 768 : 1024)
     loglik_backward_kernel(const LLArgs a, const LLShape sh, const double* __restrict__ dLL,
                            double* __restrict__ ws_g, double* __restrict__ ws_b) {
   constexpr int KM = KT > 0 ? KT : CAP_MAX_K;
@@ -186,66 +188,50 @@ __global__ void __launch_bounds__(1024)
         return nk * fast_rcp(*d + D);
       };
       float ds;
-      float dls = delta(sxs, sys, own.z, &ds);
+      const float dls = delta(sxs, sys, own.z, &ds);
       if constexpr (KT > 0) {
-        float dl[KM], cf[KM];
+        float dl[KM], ux[KM], uy[KM];
         float dmin = INFINITY;
+        // yhat_k - yhat_*  (yhat := 0 where the distance is 0)
+        const float rds = ds > 0.f ? fast_rcp(ds) : 0.f;
+        // s_*/d_* with its rounding error, so that k = * leaves exactly zero
+        const float qx = sxs * rds, qy = sys * rds;
+        const float qx_lo = fmaf(sxs, rds, -qx), qy_lo = fmaf(sys, rds, -qy);
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
           float d;
           const float4 c = st[k];
           dl[k] = delta(c.x, c.y, c.z, &d);
           dmin = fminf(dmin, dl[k]);
+          const float rk = d > 0.f ? fast_rcp(d) : 0.f;
+          if (d > 0.f && ds > 0.f) {
+            const float v = (dls - dl[k]) * (rk * rds);
+            ux[k] = fmaf(ax, v, fmaf(c.x, rk, -qx) - qx_lo);
+            uy[k] = fmaf(ay, v, fmaf(c.y, rk, -qy) - qy_lo);
+          } else {
+            ux[k] = (ax + c.x) * rk - (ax + sxs) * rds;
+            uy[k] = (ay + c.y) * rk - (ay + sys) * rds;
+          }
         }
-        dls -= dmin;
-#pragma unroll
-        for (int k = 0; k < KM; ++k) {
-          dl[k] -= dmin;
-          cf[k] = 0.f;
-        }
-        float csum = 0.f;
         for (int b = 0; b < B; ++b) {
-          const float be = beta[b], nb2 = -be * kLog2e, w = wl[b * 64];
-          float p[KM];
-          float s = 0.f, ed = 0.f;
+          // base-2 exponents with the shift folded into one FMA (p is a ratio,
+          // so the shift's rounding cancels)
+          const float be = beta[b], nb2 = -be * kLog2e, mx2 = nb2 * dmin, w = wl[b * 64];
+          float s = 0.f, ex = 0.f, ey = 0.f, ed = 0.f;
 #pragma unroll
           for (int k = 0; k < KM; ++k) {
-            p[k] = fast_exp2(nb2 * dl[k]);
-            s += p[k];
-            ed = fmaf(p[k], dl[k], ed);
+            const float p = fast_exp2(fmaf(nb2, dl[k], -mx2));
+            s += p;
+            ex = fmaf(p, ux[k], ex);
+            ey = fmaf(p, uy[k], ey);
+            ed = fmaf(p, dl[k] - dls, ed);
           }
           const float inv = 1.f / s;
-          // d log beta: beta (E[Delta] - Delta_*)
-          ab[b * nthr] += (double)(w * (be * fmaf(ed, inv, -dls)));
-          const float c = -(w * be) * inv;
-#pragma unroll
-          for (int k = 0; k < KM; ++k) cf[k] = fmaf(c, p[k], cf[k]);
+          // E[yhat] - yhat_* = ex/s ; E[Delta] - Delta_* = ed/s
+          agx -= (double)(w * (be * (ex * inv)));
+          agy -= (double)(w * (be * (ey * inv)));
+          ab[b * nthr] += (double)(w * (be * (ed * inv)));
         }
-        // sum_k cf_k (yhat_k - yhat_*): d_k = D + Delta_k (yhat := 0 where the
-        // distance is 0; the sum errs by some 1e-7 D, so 0 means below 1e-5 D)
-        const float base = D + dmin, zero = 1e-5f * D;
-        const float rds = ds > zero ? fast_rcp(ds) : 0.f;
-        const float sxs_ds = sxs * rds, sys_ds = sys * rds;
-        float ex = 0.f, ey = 0.f;
-#pragma unroll
-        for (int k = 0; k < KM; ++k) {
-          const float4 c = st[k];
-          const float d = base + dl[k];
-          const float rk = d > zero ? fast_rcp(d) : 0.f;
-          float ux, uy;
-          if (d > zero && ds > zero) {
-            const float v = (dls - dl[k]) * (rk * rds);
-            ux = fmaf(ax, v, fmaf(c.x, rk, -sxs_ds));
-            uy = fmaf(ay, v, fmaf(c.y, rk, -sys_ds));
-          } else {
-            ux = (ax + c.x) * rk - (ax + sxs) * rds;
-            uy = (ay + c.y) * rk - (ay + sys) * rds;
-          }
-          ex = fmaf(cf[k], ux, ex);
-          ey = fmaf(cf[k], uy, ey);
-        }
-        agx += (double)ex;
-        agy += (double)ey;
       } else {
         // any K: per (beta, heading), without per-heading arrays beyond dl and dk
         float dl[KM], dk[KM];
@@ -453,7 +439,7 @@ static cap_status loglik_backward_launch(const LLArgs& a, int32_t per_track_beta
   const int slices = (G + lg.slice - 1) / lg.slice;
   if (N > 0) {
     const int kt = a.m.K == 4 || a.m.K == 8 || a.m.K == 16 || a.m.K == 32 ? a.m.K : 0;
-    int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, 16);
+    int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, kt == 32 ? 8 : 16);   // (768 threads at K = 32)
     while (W > 4 && W * B > 192) W -= 4;   // sums within 96 KiB of LDS
     const dim3 grid((unsigned)N, (unsigned)slices), block(64 * W);
     const size_t lds = (size_t)B * (64 * W * sizeof(double) + 64 * sizeof(float));
