@@ -360,6 +360,19 @@ static int ll_waves(int64_t blocks, int Tmax, int L, int most) {
   return std::min(w, (chunks + 3) & ~3);
 }
 
+// Tracks of one launch: a block each, of at most 1024 threads, and a grid
+// dimension holds less than 2^32 threads.  More tracks take several launches.
+constexpr int kLaunchTracks = 1 << 21;
+
+// The arguments of the tracks from n0 on.
+static LLArgs from_track(LLArgs a, int n0) {
+  a.tracks += (size_t)n0 * (a.Tmax + 1) * 2;
+  a.lengths += n0;
+  if (a.per_track) a.log_beta += (size_t)n0 * a.B;
+  a.N -= n0;
+  return a;
+}
+
 static cap_status make_ll_args(int32_t K, double speed, double dt, const float* tracks,
                                const int32_t* lengths, int32_t N, int32_t Tmax,
                                const float* goals, int32_t G, const float* log_beta, int32_t B,
@@ -370,7 +383,7 @@ static cap_status make_ll_args(int32_t K, double speed, double dt, const float* 
   if (N < 0 || Tmax < 0) return fail(CAP_E_INVALID, "N and Tmax must be >= 0");
   if (G < 1 || G > CAP_MAX_G || B < 1 || B > CAP_MAX_B)
     return fail(CAP_E_INVALID, "G in [1, 64] and B in [1, 16] required");
-  // term counts and thread indices stay in int
+  // term counts and the second stage's thread indices stay in int
   if ((int64_t)N * G > ((int64_t)1 << 25)) return fail(CAP_E_INVALID, "N * G above 2^25");
   if (N > 0 && (!tracks || !lengths || !goals || !log_beta))
     return fail(CAP_E_INVALID, "tracks/lengths/goals/log_beta is NULL");
@@ -405,17 +418,22 @@ extern "C" cap_status cap_loglik(int32_t K, double speed, double dt, const float
   const int slices = (G + lg.slice - 1) / lg.slice;
   int W = ll_waves((int64_t)N * slices, Tmax, lg.L, 16);
   while (W > 4 && W * B * (64 + lg.slice) > 12288) W -= 4;   // sums within 96 KiB of LDS
-  const dim3 grid((unsigned)N, (unsigned)slices), block(64 * W);
+  const dim3 block(64 * W);
   const size_t lds = (size_t)W * (64 + lg.slice) * B * sizeof(double);
   hipStream_t s = as_stream(stream);
-  switch (a.m.U) {
-    case 4: hipLaunchKernelGGL(loglik_kernel<4>, grid, block, lds, s, a, lg, LL_dev); break;
-    case 8: hipLaunchKernelGGL(loglik_kernel<8>, grid, block, lds, s, a, lg, LL_dev); break;
-    case 16: hipLaunchKernelGGL(loglik_kernel<16>, grid, block, lds, s, a, lg, LL_dev); break;
-    case 32: hipLaunchKernelGGL(loglik_kernel<32>, grid, block, lds, s, a, lg, LL_dev); break;
-    default: hipLaunchKernelGGL(loglik_kernel<0>, grid, block, lds, s, a, lg, LL_dev); break;
+  for (int n0 = 0; n0 < N; n0 += kLaunchTracks) {
+    const LLArgs q = from_track(a, n0);
+    const dim3 grid((unsigned)std::min(q.N, kLaunchTracks), (unsigned)slices);
+    double* out = LL_dev + (size_t)n0 * B * G;
+    switch (q.m.U) {
+      case 4: hipLaunchKernelGGL(loglik_kernel<4>, grid, block, lds, s, q, lg, out); break;
+      case 8: hipLaunchKernelGGL(loglik_kernel<8>, grid, block, lds, s, q, lg, out); break;
+      case 16: hipLaunchKernelGGL(loglik_kernel<16>, grid, block, lds, s, q, lg, out); break;
+      case 32: hipLaunchKernelGGL(loglik_kernel<32>, grid, block, lds, s, q, lg, out); break;
+      default: hipLaunchKernelGGL(loglik_kernel<0>, grid, block, lds, s, q, lg, out); break;
+    }
+    CAP_HIP(hipGetLastError());
   }
-  CAP_HIP(hipGetLastError());
   return CAP_OK;
 }
 
@@ -441,16 +459,23 @@ static cap_status loglik_backward_launch(const LLArgs& a, int32_t per_track_beta
     const int kt = a.m.K == 4 || a.m.K == 8 || a.m.K == 16 || a.m.K == 32 ? a.m.K : 0;
     int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, kt == 32 ? 8 : 16);   // (768 threads at K = 32)
     while (W > 4 && W * B > 192) W -= 4;   // sums within 96 KiB of LDS
-    const dim3 grid((unsigned)N, (unsigned)slices), block(64 * W);
+    const dim3 block(64 * W);
     const size_t lds = (size_t)B * (64 * W * sizeof(double) + 64 * sizeof(float));
-    switch (kt) {
-      case 4: hipLaunchKernelGGL(loglik_backward_kernel<4>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 8: hipLaunchKernelGGL(loglik_backward_kernel<8>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 16: hipLaunchKernelGGL(loglik_backward_kernel<16>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      case 32: hipLaunchKernelGGL(loglik_backward_kernel<32>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
-      default: hipLaunchKernelGGL(loglik_backward_kernel<0>, grid, block, lds, s, a, lg, dLL_dev, ws_g, ws_b); break;
+    for (int n0 = 0; n0 < N; n0 += kLaunchTracks) {
+      const LLArgs q = from_track(a, n0);
+      const dim3 grid((unsigned)std::min(q.N, kLaunchTracks), (unsigned)slices);
+      const double* d = dLL_dev + (size_t)n0 * B * G;
+      double* wg = ws_g + (size_t)n0 * G * 2;
+      double* wb = ws_b + (size_t)n0 * slices * B;
+      switch (kt) {
+        case 4: hipLaunchKernelGGL(loglik_backward_kernel<4>, grid, block, lds, s, q, lg, d, wg, wb); break;
+        case 8: hipLaunchKernelGGL(loglik_backward_kernel<8>, grid, block, lds, s, q, lg, d, wg, wb); break;
+        case 16: hipLaunchKernelGGL(loglik_backward_kernel<16>, grid, block, lds, s, q, lg, d, wg, wb); break;
+        case 32: hipLaunchKernelGGL(loglik_backward_kernel<32>, grid, block, lds, s, q, lg, d, wg, wb); break;
+        default: hipLaunchKernelGGL(loglik_backward_kernel<0>, grid, block, lds, s, q, lg, d, wg, wb); break;
+      }
+      CAP_HIP(hipGetLastError());
     }
-    CAP_HIP(hipGetLastError());
   }
   // with N = 0 the sums are empty: the kernels write zeros
   const int long_sums = 2 * G + (per_track_beta ? 0 : B);
