@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(1024)
   double* part = dyn + (size_t)B * nthr;
   for (int b = threadIdx.x; b < B; b += nthr) beta[b] = expf(lb[b]);
   for (int b = 0; b < B; ++b) acc[b * nthr] = 0.0;
-  load_steps(a.m, st);
+  if constexpr (KT > 0) load_steps(a.m, st);   // (the general form reads the arguments)
   for (int t0 = 0; t0 < len; t0 += kStepBuf) {
     const int tn = min(kStepBuf, len - t0);
     __syncthreads();
@@ -138,8 +138,8 @@ __global__ void __launch_bounds__(KT > 16 ? 768 : 1024)
   __shared__ uint8_t ks[kStepBuf];
   __shared__ float4 st[CAP_MAX_K];
   __shared__ float beta[CAP_MAX_B];
-  __shared__ double red[16][2 * 64];
-  extern __shared__ double dyn[];    // ab [B][threads], then w [B][64] (FP32)
+  // sums [waves][2 x 64], then ab [B][threads], then w [B][64] (FP32)
+  extern __shared__ double lds[];
   const int nthr = blockDim.x, W = nthr >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = blockIdx.x, g0 = (int)blockIdx.y * sh.slice, gn = min(sh.slice, a.G - g0);
@@ -147,6 +147,8 @@ __global__ void __launch_bounds__(KT > 16 ? 768 : 1024)
   const bool on = gl < gn;
   const int g = g0 + (on ? gl : 0);
   const int K = KT > 0 ? KT : a.m.K;
+  double* red = lds;
+  double* dyn = lds + 2 * nthr;
   const int len = a.lengths[n];
   const float* z = a.tracks + (size_t)n * (a.Tmax + 1) * 2;
   const float* lb = a.per_track ? a.log_beta + (size_t)n * B : a.log_beta;
@@ -275,13 +277,13 @@ __global__ void __launch_bounds__(KT > 16 ? 768 : 1024)
   }
   const double sgx = goal_sum(agx, sub, sh.L), sgy = goal_sum(agy, sub, sh.L);
   if (on && sub == 0) {
-    red[wave][2 * gl] = sgx;
-    red[wave][2 * gl + 1] = sgy;
+    red[wave * 128 + 2 * gl] = sgx;
+    red[wave * 128 + 2 * gl + 1] = sgy;
   }
   __syncthreads();
   for (int i = tid; i < 2 * gn; i += nthr) {
-    double s = red[0][i];
-    for (int w = 1; w < W; ++w) s += red[w][i];
+    double s = red[i];
+    for (int w = 1; w < W; ++w) s += red[w * 128 + i];
     ws_g[((size_t)n * a.G + g0) * 2 + i] = s;
   }
   // d log beta of the slice: a wave per beta sums the threads' entries
@@ -341,23 +343,33 @@ __global__ void loglik_track_beta_kernel(int N, int B, int slices,
 // keeps at least three lanes (60 or more of the 64 busy); more slices than that
 // only while the tracks leave CUs without a block (each slice recovers the
 // track's controls again).
-static LLShape ll_shape(int N, int G) {
-  const int fill = std::min(G, (256 + std::max(N, 1) - 1) / std::max(N, 1));
+static LLShape ll_shape(int N, int G, int cus) {
+  const int fill = std::min(G, (cus + std::max(N, 1) - 1) / std::max(N, 1));
   const int slices = std::max((G + 20) / 21, fill);
   const int per = (G + slices - 1) / slices;
   return LLShape{64 / per, per};
 }
 
-// Waves per block: four (one per SIMD), or more for the chunks of steps while
-// the tracks alone leave the device's wave slots unfilled -- always whole fours:
-// a block's waves go to the SIMDs in turn, so five of them crowd one SIMD (five
-// rounds instead of seven, but 102 us instead of 90 forward and 242 instead of 152
-// in the adjoint at 1024 tracks).
-static int ll_waves(int64_t blocks, int Tmax, int L, int most) {
+// Waves per block.  At most four (one per SIMD), as few as take the chunks in
+// that many rounds: a further wave would only idle (100000 tracks x 5 steps, one
+// goal, K = 32, forward: 432 us with four waves a block, 139 with one), and an
+// uneven split leaves the first waves, which sit on the same SIMDs in every
+// block, the longest (800 tracks x 100 steps x 5 goals, K = 32, adjoint: nine
+// chunks to four waves 49 us, to three 40).  More only while the blocks do not
+// fill the device, in whole fours (a block's waves go to the SIMDs in turn: five
+// waves at 1024 tracks 102 us instead of 90 forward and 242 instead of 152 in the
+// adjoint): eight while blocks of four leave wave slots empty (`per_cu` of them on
+// a CU, two blocks or more), and further only where the blocks still fit the
+// device together (300 tracks x 100 steps x 21 goals, K = 32: 65 us with 16
+// waves, 59 with 8).
+static int ll_waves(int64_t blocks, int Tmax, int L, int cus, int per_cu, int most) {
   const int chunks = std::max(1, (Tmax + L - 1) / L);
-  int w = 4;
-  while (w < most && w < chunks && blocks * w < 4096) w *= 2;
-  return std::min(w, (chunks + 3) & ~3);
+  const int rounds = (chunks + 3) / 4;
+  int w = (chunks + rounds - 1) / rounds;
+  if (chunks >= 16 && per_cu >= 16 && blocks * 4 < (int64_t)cus * per_cu) w = 8;
+  for (int c = 8; c <= most; c += 4)
+    if (w < c && c - 4 < chunks && blocks <= (int64_t)cus * (per_cu / c)) w = c;
+  return w;
 }
 
 // Tracks of one launch: a block each, of at most 1024 threads, and a grid
@@ -414,9 +426,10 @@ extern "C" cap_status cap_loglik(int32_t K, double speed, double dt, const float
   if (st != CAP_OK) return st;
   if (N == 0) return CAP_OK;
   if (!LL_dev) return fail(CAP_E_INVALID, "LL is NULL");
-  const LLShape lg = ll_shape(N, G);
+  const int cus = std::max(1, cap_device_cu_count());
+  const LLShape lg = ll_shape(N, G, cus);
   const int slices = (G + lg.slice - 1) / lg.slice;
-  int W = ll_waves((int64_t)N * slices, Tmax, lg.L, 16);
+  int W = ll_waves((int64_t)N * slices, Tmax, lg.L, cus, 16, 16);
   while (W > 4 && W * B * (64 + lg.slice) > 12288) W -= 4;   // sums within 96 KiB of LDS
   const dim3 block(64 * W);
   const size_t lds = (size_t)W * (64 + lg.slice) * B * sizeof(double);
@@ -453,14 +466,17 @@ static cap_status loglik_backward_launch(const LLArgs& a, int32_t per_track_beta
   const int32_t N = a.N, G = a.G, B = a.B;
   double* ws_g = static_cast<double*>(ws_dev);
   double* ws_b = ws_g + (size_t)N * G * 2;
-  const LLShape lg = ll_shape(N, G);
+  const int cus = std::max(1, cap_device_cu_count());
+  const LLShape lg = ll_shape(N, G, cus);
   const int slices = (G + lg.slice - 1) / lg.slice;
   if (N > 0) {
     const int kt = a.m.K == 4 || a.m.K == 8 || a.m.K == 16 || a.m.K == 32 ? a.m.K : 0;
-    int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, kt == 32 ? 8 : 16);   // (768 threads at K = 32)
+    const int most = kt == 32 ? 12 : 16;   // waves per CU (and of a block)
+    int W = ll_waves((int64_t)N * slices, a.Tmax, lg.L, cus, most, most);
     while (W > 4 && W * B > 192) W -= 4;   // sums within 96 KiB of LDS
     const dim3 block(64 * W);
-    const size_t lds = (size_t)B * (64 * W * sizeof(double) + 64 * sizeof(float));
+    const size_t lds = (size_t)W * 128 * sizeof(double) +
+                       (size_t)B * (64 * W * sizeof(double) + 64 * sizeof(float));
     for (int n0 = 0; n0 < N; n0 += kLaunchTracks) {
       const LLArgs q = from_track(a, n0);
       const dim3 grid((unsigned)std::min(q.N, kLaunchTracks), (unsigned)slices);
