@@ -264,8 +264,10 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
 // of all K headings follow from a few harmonics of the heading angle.  With
 // r = |a|, x = |s| / r and psi the angle between a and s_k,
 //   (|a + s_k| - |a|) / |s| = (1 - x^2/8) cos psi - (x/4) cos 2 psi
-//                             + (x^2/8) cos 3 psi + const + e,  |e| <= 0.098 x^3
-// (x <= 0.15; the constant cancels in the policy).  Of a particle's features
+//                             + (x^2/8) cos 3 psi + const + e,  |e| <= 0.1154 x^3
+// (x <= 0.12; the constant cancels in the policy, and e is what is left at the best
+// one: its x^3 term is (1 - c^2) (5 c^2 - 1) / 8, c = cos psi, which alone spans
+// 0.2251 x^3).  Of a particle's features
 // f_m = nb |s| (...) u^m (u the unit vector of a) the exponents of the four
 // headings theta + 90 j are even + odd, -even + odd', even - odd and
 // -even - odd', so that 16 headings take 36 operations instead of the 96 and the
@@ -277,7 +279,7 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
 // inverse CDF is taken only where u lies farther than `tol` (relative to the
 // total) from the CDF boundaries beside it, a bound on the difference of the two
 // computations; otherwise the caller runs draw_headings.  So the headings are
-// draw_headings' in every case, bit for bit.  tol = c0 + |nb s| (c1 + 0.035 x^3):
+// draw_headings' in every case, bit for bit.  tol = c0 + |nb s| (c1 + 0.0405 x^3):
 //   * draw_headings itself: each exponent within 6.1 2^-23 |nb s| (dot product,
 //     square roots and reciprocal within 1 ulp, products), so with a weight's
 //     relative error w a CDF value errs by at most w/2; exp2 within 1 ulp; K - 1
@@ -285,8 +287,10 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
 //   * here: features and their sums within 13 2^-24 |nb s|, the cut-off e |nb s|,
 //     the lattice's rounding of the steps (0.71 units, 0.71 |nb|), exp2 and the
 //     same additions.
-// Together K 2.4e-7 + 2e-7 + |nb s| (6e-7 + 0.034 x^3 + 0.25 / |s|); the host
-// takes 1.25 times the rounding terms.  At most 2 (K - 1) tol of the draws fall
+// Exponents are base 2, so an error of v |nb s| in them is w = ln 2 v |nb s| in a
+// weight.  Together K 2.4e-7 + 2e-7 + |nb s| (6e-7 + 0.0400 x^3 + 0.25 / |s|); the
+// host takes 1.25 times the rounding terms.  (The cut-off's part is not reached:
+// the largest found over psi, x, |nb s| and K = 8, 16, 32 is 0.016 |nb s| x^3.)  At most 2 (K - 1) tol of the draws fall
 // back: 2e-4 at K = 16 and small |nb s|.
 //
 // Bound by VALU issue as before, with fewer slots: 120 instructions a draw
@@ -297,10 +301,10 @@ __device__ __forceinline__ void draw_headings(const float* ax, const float* ay, 
 struct FarConst {
   float d2;       // smallest |a|^2 (lattice units) the filter takes; inf: none
   float s4;       // -|s| / 4
-  float c0, c1;   // tol = c0 + |nb s| (c1 + 0.035 x^3)
+  float c0, c1;   // tol = c0 + |nb s| (c1 + kFarCut x^3)
 };
 constexpr float kFarX = 0.12f;       // largest x
-constexpr float kFarCut = 0.035f;
+constexpr float kFarCut = 0.0405f;
 
 // cos(11.25 i degrees), i = 0..8
 constexpr float kCos32[9] = {1.f,          0.98078528f, 0.92387953f, 0.83146961f, 0.70710678f,
