@@ -36,8 +36,15 @@ __global__ void __launch_bounds__(256) normalize_kernel(const uint32_t* __restri
   for (size_t v = head * 4 + i; v < n; v += stride) p[v] = (float)c[v] / N;
 }
 
+// Threads of a block at most.  The shifted draw of several speeds keeps its
+// exponents over two passes (239 and 256 registers at K = 16 and 32): with the 128
+// of 1024-thread blocks it spills (400000 particles x 20 steps of 6 x 16 controls
+// 3.27 ms, with 256 threads 1.22).
+template <int KT, bool SHIFT, bool MS>
+constexpr int plain_threads() { return SHIFT && MS && KT >= 16 ? 256 : 1024; }
+
 template <int KT, int P, bool SHIFT, bool MS, int L>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__((plain_threads<KT, SHIFT, MS>()))
     rollout_plain_kernel(const RolloutDesc d, uint32_t seed_lo, uint32_t seed_hi, int cap) {
   __shared__ TileShared sh;
   __shared__ float4 ctl[MS ? CAP_MAX_U : 1];
@@ -140,6 +147,7 @@ static int plain_window_words(const RolloutDesc& d, int threads) {
 template <int KT, int P, bool MS, int L = 1>
 static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t shi, int threads,
                                  hipStream_t s) {
+  if (L == 1 && d.shift) threads = std::min(threads, plain_threads<KT, true, MS>());
   const int64_t per_block = (int64_t)P * (threads / L);
   const int64_t blocks = (d.N + per_block - 1) / per_block;
   const int cap = plain_window_words(d, threads);
