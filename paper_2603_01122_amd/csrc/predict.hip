@@ -48,8 +48,11 @@ __global__ void __launch_bounds__((plain_threads<KT, SHIFT, MS>()))
     rollout_plain_kernel(const RolloutDesc d, uint32_t seed_lo, uint32_t seed_hi, int cap) {
   __shared__ TileShared sh;
   __shared__ float4 ctl[MS ? CAP_MAX_U : 1];
-  extern __shared__ uint32_t win[];
-  for (int i = threadIdx.x; i < 2 * cap; i += blockDim.x) win[i] = 0u;
+  extern __shared__ __align__(16) uint32_t win[];
+  // cap is a multiple of four: whole 16-byte stores (a block of one wave clears
+  // the 38 KB of 20 steps in 37 of them)
+  for (int i = threadIdx.x; i < cap / 2; i += blockDim.x)
+    reinterpret_cast<uint4*>(win)[i] = make_uint4(0u, 0u, 0u, 0u);
   // the first barrier inside rollout_tile orders this clear before any binning
   const int64_t first = (int64_t)blockIdx.x * P * (blockDim.x / L);
   rollout_tile<KT, P, SHIFT, MS, L>(d, first, seed_lo, seed_hi, sh, win, cap, ctl);
