@@ -127,23 +127,28 @@ static cap_status launch_zero(uint32_t* p, size_t n, uint32_t* q, size_t m, hipS
   return CAP_OK;
 }
 
-// Words of one window buffer for blocks of `threads`: what the widest step
-// window needs, at most the share of a CU's LDS that leaves the other blocks of
-// that size their place (a 1024-thread block is alone on its CU at 128
-// registers).  A window of up to twice the buffer still fits (see
+// Words of one window buffer at most: the share of a CU's LDS that leaves the
+// other blocks of that size their place (a 1024-thread block is alone on its CU at
+// 128 registers).  A window of up to twice the buffer still fits (see
 // rollout_tile_body).
+static constexpr int most_window_words(int threads) {
+  return (threads <= 256 ? 40 : threads <= 512 ? 64 : 128) * 1024 / (2 * (int)sizeof(uint32_t));
+}
+
+// Words of the last step's window, the widest.
+static int64_t reach_words(const RolloutDesc& d) {
+  const int64_t rx = (int64_t)d.H * d.Rx, ry = (int64_t)d.H * d.Ry;
+  const int64_t x0 = std::max<int64_t>((d.X0 - rx) >> kLatticeShift, 0),
+                x1 = std::min<int64_t>((d.X0 + rx) >> kLatticeShift, d.nx - 1),
+                y0 = std::max<int64_t>((d.Y0 - ry) >> kLatticeShift, 0),
+                y1 = std::min<int64_t>((d.Y0 + ry) >> kLatticeShift, d.ny - 1);
+  return x1 < x0 || y1 < y0 ? 0 : (x1 - x0 + 2) / 2 * (y1 - y0 + 1);
+}
+
+// Words of one window buffer for blocks of `threads`: what the widest step window
+// needs, at most the above.
 static int plain_window_words(const RolloutDesc& d, int threads) {
-  const int most = (threads <= 256 ? 40 : threads <= 512 ? 64 : 128) * 1024 / (2 * (int)sizeof(uint32_t));
-  int need = 0;
-  for (int t = d.H; t >= 1 && need < most; --t) {
-    const int64_t rx = (int64_t)t * d.Rx, ry = (int64_t)t * d.Ry;
-    const int64_t x0 = std::max<int64_t>((d.X0 - rx) >> kLatticeShift, 0),
-                  x1 = std::min<int64_t>((d.X0 + rx) >> kLatticeShift, d.nx - 1),
-                  y0 = std::max<int64_t>((d.Y0 - ry) >> kLatticeShift, 0),
-                  y1 = std::min<int64_t>((d.Y0 + ry) >> kLatticeShift, d.ny - 1);
-    if (x1 < x0 || y1 < y0) continue;
-    need = (int)std::max<int64_t>(need, std::min<int64_t>((x1 - x0 + 2) / 2 * (y1 - y0 + 1), most));
-  }
+  const int need = (int)std::min<int64_t>(reach_words(d), most_window_words(threads));
   return std::max(64, (need + 3) & ~3);
 }
 
@@ -177,47 +182,67 @@ static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t sh
 // blocks of 256 threads issue 4.75e6 atomics and the call takes 337-378 us, with
 // 256 blocks of 1024 threads 214; 8192 particles x 10 steps (96 controls): 32
 // blocks of 256 threads 73.9 us, 128 of 64 threads 69.0.
+//
+// Where larger tiles do not pay, blocks stay smaller, as several of them on a CU
+// fill each other's waits:
+//   * a reach beyond the largest windows (both buffers), at 16 headings or more:
+//     the particles spread until they share few cells (2^18 particles x 60 steps of
+//     2.4 cells on 500 x 500 cells, K = 16: 1024 threads 777 us, 256 threads 720;
+//     K = 4 622 and 772), up to 64 waves a CU (2 10^6 particles: 4.82 and 4.90 ms);
+//   * several speeds, for their longer draws: more than 64 controls 256 threads
+//     (70000 particles x 10 steps of 6 x 16 controls: 512 threads 84 us, 256 threads
+//     76; 2^20 x 20 steps 1024 threads 1.03 ms, 512 and 256 0.97), 64 controls of 16
+//     headings or more and the shifted draw 512 (2^20 x 20 steps of 4 x 16: 1024 threads
+//     0.82 ms, 512 0.78, 256 1.07; of 2 x 8, sharp: 416, 382 and 413 us), else 1024 (of 2 x
+//     16: 0.63, 0.82 and 1.00 ms; 50 steps of 8 x 8: 1.92, 2.27 and 2.65).
 template <int KT, bool MS>
-static cap_status launch_plain_k(const RolloutDesc& d, uint32_t slo, uint32_t shi,
+static cap_status launch_plain_k(const RolloutDesc& d, int64_t cus, uint32_t slo, uint32_t shi,
                                  hipStream_t s) {
-  const int64_t cus = std::max(1, cap_device_cu_count());
   const int64_t waves = (d.N + 64 * cus - 1) / (64 * cus);   // per CU
+  int most = 1024;
   if constexpr (MS) {
-    // few particles: several lanes each, while those fit two (eight lanes) or four
-    // waves per SIMD; 8192 particles x 10 steps of 96 controls: 52 us by one lane,
-    // 34 by eight.
+    // few particles: several lanes each, eight while those fit two waves per SIMD, then
+    // four up to two (8 headings) or two and a half; 8192 particles x 10 steps of 96
+    // controls: 52 us by one lane, 34 by eight; one lane | four, 12 steps: 6 x 16 controls,
+    // 40000 particles 66 | 61 us, 65536 75 | 77; 3 x 32 controls, 32768 72 | 57, 40000 72 |
+    // 72, 65536 79 | 91; 50 steps of 2 x 8 controls, 45000 131 | 144
     const auto threads = [&](int L) {
       return 64 * (int)std::min<int64_t>((L * d.N + 64 * cus - 1) / (64 * cus), 16);
     };
     if constexpr (KT >= 16)
       if (!d.shift && d.N <= 64 * cus) return launch_plain_t<KT, 1, MS, 8>(d, slo, shi, threads(8), s);
     if constexpr (KT >= 8)
-      if (!d.shift && d.N <= 256 * cus) return launch_plain_t<KT, 1, MS, 4>(d, slo, shi, threads(4), s);
+      if (!d.shift && d.N <= (KT == 8 ? 128 : 160) * cus)
+        return launch_plain_t<KT, 1, MS, 4>(d, slo, shi, threads(4), s);
+    if (d.K * d.S > 64) most = 256;
+    else if (d.shift || (KT >= 16 && d.K * d.S == 64)) most = 512;
+  } else {
+    const bool wide = (KT == 0 || KT >= 16) && reach_words(d) > 2 * most_window_words(1024);
+    if (wide && waves <= 64) most = 256;
+    else if (waves > 32) return launch_plain_t<KT, 4, MS>(d, slo, shi, 1024, s);
+    else if (waves > 16) return launch_plain_t<KT, 2, MS>(d, slo, shi, 1024, s);
   }
-  if constexpr (!MS) {
-    if (waves > 32) return launch_plain_t<KT, 4, MS>(d, slo, shi, 1024, s);
-    if (waves > 16) return launch_plain_t<KT, 2, MS>(d, slo, shi, 1024, s);
-  }
-  return launch_plain_t<KT, 1, MS>(d, slo, shi, 64 * (int)std::min<int64_t>(waves, 16), s);
+  return launch_plain_t<KT, 1, MS>(d, slo, shi, (int)std::min<int64_t>(64 * waves, most), s);
 }
 
 static cap_status launch_plain(const RolloutDesc& d, uint32_t slo, uint32_t shi, hipStream_t s) {
+  const int cus = std::max(1, cap_device_cu_count());
   // specialised kernels assume a point-symmetric step table; several speeds
   // need one (checked when the descriptor is built)
   if (d.S > 1) {
     switch (d.K) {
-      case 4: return launch_plain_k<4, true>(d, slo, shi, s);
-      case 8: return launch_plain_k<8, true>(d, slo, shi, s);
-      case 16: return launch_plain_k<16, true>(d, slo, shi, s);
-      default: return launch_plain_k<32, true>(d, slo, shi, s);
+      case 4: return launch_plain_k<4, true>(d, cus, slo, shi, s);
+      case 8: return launch_plain_k<8, true>(d, cus, slo, shi, s);
+      case 16: return launch_plain_k<16, true>(d, cus, slo, shi, s);
+      default: return launch_plain_k<32, true>(d, cus, slo, shi, s);
     }
   }
   switch (d.sym ? d.K : 0) {
-    case 4: return launch_plain_k<4, false>(d, slo, shi, s);
-    case 8: return launch_plain_k<8, false>(d, slo, shi, s);
-    case 16: return launch_plain_k<16, false>(d, slo, shi, s);
-    case 32: return launch_plain_k<32, false>(d, slo, shi, s);
-    default: return launch_plain_k<0, false>(d, slo, shi, s);
+    case 4: return launch_plain_k<4, false>(d, cus, slo, shi, s);
+    case 8: return launch_plain_k<8, false>(d, cus, slo, shi, s);
+    case 16: return launch_plain_k<16, false>(d, cus, slo, shi, s);
+    case 32: return launch_plain_k<32, false>(d, cus, slo, shi, s);
+    default: return launch_plain_k<0, false>(d, cus, slo, shi, s);
   }
 }
 
