@@ -748,6 +748,7 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
     H->union_out = nullptr;
     H->union_H = H->union_nx = H->union_ny = 0;
   }
+  for (int i = 0; i < n; ++i) out[i].rd.bounds = bounds_rule(parts, p->n_cus);
   // several speeds: few particles take the wide variant
   if (variant == 0 && p->rollout_fn[kWideVariant] && parts <= kWideParticles)
     variant = kWideVariant;

@@ -18,6 +18,7 @@ struct RolloutDesc {
   int32_t X0, Y0;           // start on the lattice (grid frame)
   int32_t Rx, Ry;           // max |S_kx|, |S_ky|: reach per step, lattice units
   uint32_t human, cycle;
+  int32_t bounds;           // bounds_rule: windows from the tile's true bounds
   int32_t shift;            // 1: subtract the largest exponent (large beta * step)
   int32_t sym;              // 1: S_{k+K/2} = -S_k for every k < K/2 (K even)
   HeadingTable T;           // lattice-unit steps (exact integers) and squared lengths (FP32)
@@ -30,6 +31,22 @@ struct RolloutDesc {
   uint8_t* trace_k;         // [N][H] or null
   int32_t* trace_pair;      // [N] or null
 };
+
+// When the tiles of a launch of so many particles take their true bounds (see
+// rollout_tile_body).  Few particles: never; a step's latency is what counts and
+// their atomics are cheap.  From one wave per CU on: where the particles share
+// cells, as atomics on the same word wait for each other.  From eight waves per CU
+// on: always, as the atomics' number is what counts.  60 steps of 2.4 cells on 200
+// x 200 cells, never | always: flat belief (K = 16), 8000 particles 72 | 85 us, 30000
+// 108 | 115, 2^17 342 | 351, 2^18 549 | 547, 600000 859 | 844; sharp (beta * step 3.6
+// to 72), 8000 84 | 95, 30000 147 | 91, 2^17 578 | 132.  A plan of blocks of 512 threads
+// and 24 KiB windows, 16 humans x 30000, K = 8: 906 | 809 us.
+enum : int32_t { kBoundsNever = 0, kBoundsShared = 1, kBoundsAlways = 2 };
+
+inline int32_t bounds_rule(int64_t particles, int cus) {
+  if (particles >= (int64_t)512 * cus) return kBoundsAlways;
+  return particles >= (int64_t)64 * cus ? kBoundsShared : kBoundsNever;
+}
 
 struct TileShared {
   double P[CAP_MAX_J];      // pair CDF (sequential FP64 prefix sums), then the sort's counts
@@ -182,7 +199,8 @@ __device__ __forceinline__ void sort_by_pair(int tid, int64_t first, int tile_n,
 // which went to global atomics one particle at a time, at the 2.7e10 a second
 // that the device takes, stay in LDS: 16 humans x 10^5 particles x 100 steps of
 // 2.4 cells on 256 x 256 cells, a cycle of 4.21 ms before and 2.42 after; eight
-// humans of the 64-human scene 16.2 -> 15.9 ms.
+// humans of the 64-human scene 16.2 -> 15.9 ms.  Launches of few particles do so
+// only where it pays (bounds_rule).
 //
 // MS (several speeds): draw_control over the S K controls; `ctl` is an LDS
 // array of CAP_MAX_U float4 that receives (fx, fy, s2) of every control, read
@@ -321,9 +339,18 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
       for (int p = 0; p < P; ++p)
         rw[p] = philox10(idx[p], (uint32_t)((t - 1) >> 2), human, c3_head, klo, khi);
       // The windows outgrow the buffer within these four steps: take the
-      // particles' true bounds.
-      if (t > 1 && window_words(step_window_of(lox, loy, hix, hiy, Rx, Ry, nx, ny,
-                                               min(t + 3, H) - t_box)) > cap) {
+      // particles' true bounds, or (kBoundsShared) only if the words that the last
+      // step touched held two particles or more on average; its count is cleared
+      // after this step's barrier, and 0 if that step used global atomics.  (The rule
+      // is read here and off the straight path: held in a register, eight humans of
+      // 2^20 particles, K = 32, took 15.97 ms instead of 15.55.)
+      bool take = t > 1 && window_words(step_window_of(lox, loy, hix, hiy, Rx, Ry, nx, ny,
+                                                       min(t + 3, H) - t_box)) > cap;
+      if (take && __builtin_expect(d.bounds != kBoundsAlways, 0)) {
+        const int touched = __builtin_amdgcn_readfirstlane(sh.ntouch[m3 == 0 ? 2 : m3 - 1]);
+        take = d.bounds == kBoundsShared && touched > 0 && 2 * touched <= tile_n;
+      }
+      if (take) {
         int b[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};
 #pragma unroll
         for (int p = 0; p < P; ++p)
