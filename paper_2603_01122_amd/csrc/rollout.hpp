@@ -4,6 +4,8 @@
 // window flushed to the global uint32 grid with coalesced atomics.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace capred {
@@ -312,15 +314,17 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   if constexpr (L > 1) rows.load(ctl, d.S, tid % L);
   // The descriptor's fields that every step reads, in scalar registers for the
   // whole tile: it lies in memory that the loop's stores could alias, so each
-  // use would be a load and a wait.
-  const int H = d.H, nx = d.nx, ny = d.ny, Rx = d.Rx, Ry = d.Ry;
-  const uint32_t human = d.human;
-  uint32_t* const counts = d.counts;
-  uint8_t* const trace_k = d.trace_k;
+  // use would be a load and a wait.  Several speeds read them from there: their
+  // controls' table fills the scalar registers, and what is held besides goes to
+  // vector-register lanes, one VALU access each (K = 16: 55 more a step; 16 humans
+  // x 30000 particles of 6 x 16 controls, 30 steps: 782 us read, 823 held).
+  using Int = std::conditional_t<MS, const int32_t&, const int32_t>;
+  Int H = d.H, nx = d.nx, ny = d.ny, Rx = d.Rx, Ry = d.Ry, S = d.S, s_last = d.s_last;
+  std::conditional_t<MS, const uint32_t&, const uint32_t> human = d.human, smask = d.smask;
+  std::conditional_t<MS, uint32_t* const&, uint32_t* const> counts = d.counts;
+  std::conditional_t<MS, uint8_t* const&, uint8_t* const> trace_k = d.trace_k;
   const FarConst fc = d.far;
-  const int S = d.S, s_last = d.s_last;
-  const uint32_t smask = d.smask;
-  const size_t plane = (size_t)nx * (size_t)ny;
+  const size_t plane = MS ? 0 : (size_t)nx * (size_t)ny;   // (several speeds: each step's own)
   uint4 rw[P];
   const int list_cap = P * nthr;
   int m3 = 1;  // t mod 3
@@ -386,7 +390,7 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
     uint16_t* list = single ? lists : lists + (t & 1) * list_cap;
     // both buffers: the previous step's flush (of either buffer) must be over
     if (single) __syncthreads();
-    uint32_t* grid_t = counts + (size_t)(t - 1) * plane;
+    uint32_t* grid_t = counts + (size_t)(t - 1) * (MS ? (size_t)nx * (size_t)ny : plane);
     // Draws of all P particles first, then their emplacement: the draws are
     // independent dependency chains (transcendental latency), which the
     // scheduler can interleave only while no branch separates them.  Each
