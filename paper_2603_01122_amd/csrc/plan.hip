@@ -424,11 +424,12 @@ struct HostSlot {
 // Rollout variants of a plan's launches: plain, shifted exponent, and (several
 // speeds) kWideLanes lanes per particle.
 constexpr int kVariants = 3, kWideVariant = 2, kWideLanes = 4;
-// Particles of a cycle up to which the wide variant runs: with four lanes each
-// they fill four waves on each SIMD; beyond, the lanes repeat the chain of
+// Particles of a cycle per CU up to which the wide variant runs: with four lanes
+// each they fill four waves on each SIMD; beyond, the lanes repeat the chain of
 // additions for nothing.  Five humans of 8192 particles x 6 steps, 96 controls:
-// rollout 92 -> 49 us.
-constexpr int64_t kWideParticles = 65536;
+// rollout 92 -> 49 us; eight (the limit at 256 CUs) x 30 steps, the cycle 222 us, by
+// one lane 438.
+constexpr int kWidePerCu = 256;
 // LDS windows of a plan whose caller leaves them open: with the whole shape open,
 // and otherwise (see cap_plan_create).
 constexpr int kOpenLds = 128 * 1024, kPlainLds = 40 * 1024;
@@ -749,8 +750,8 @@ static size_t build_entry(cap_plan* p, int e, uint64_t seed, uint32_t cycle) {
     H->union_H = H->union_nx = H->union_ny = 0;
   }
   for (int i = 0; i < n; ++i) out[i].rd.bounds = bounds_rule(parts, p->n_cus);
-  // several speeds: few particles take the wide variant
-  if (variant == 0 && p->rollout_fn[kWideVariant] && parts <= kWideParticles)
+  if (variant == 0 && p->rollout_fn[kWideVariant] &&
+      parts <= (int64_t)kWidePerCu * p->n_cus)
     variant = kWideVariant;
   p->last_variant = variant;
   // tile kinds of the persistent launch
