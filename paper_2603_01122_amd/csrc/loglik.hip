@@ -123,11 +123,13 @@ __global__ void __launch_bounds__(1024)
 // KT > 0 (the model has KT headings, every loop over them unrolled): the unit
 // vectors' differences are formed once per heading (from each distance's own
 // square root; the chosen heading's is exactly zero).  Per beta the KT
-// probabilities give four moments, which are added over betas and steps in
-// FP64; the per-lane sums of d log beta are kept in LDS.  Four arrays of KT
+// probabilities give four moments, of even and odd headings apart and Delta
+// relative to its minimum (shorter FP32 sums; where the chosen heading is the
+// unlikely one its part is not rounded with the sum), which are added over betas
+// and steps in FP64; the per-lane sums of d log beta are kept in LDS.  Four arrays of KT
 // values live over the betas: at K = 32, 160 registers and three waves per SIMD,
 // so blocks of at most 768 threads (1024 tracks x 200 steps x 8 goals x 9 betas:
-// 149 us; at 128 registers, the differences of Delta formed anew for every beta,
+// 150 us; at 128 registers, the differences of Delta formed anew for every beta,
 // 160).  One coefficient per heading in place of the two goal moments takes 135,
 // but adds the betas in FP32.
 template <int KT>
@@ -219,20 +221,20 @@ __global__ void __launch_bounds__(KT > 16 ? 768 : 1024)
           // base-2 exponents with the shift folded into one FMA (p is a ratio,
           // so the shift's rounding cancels)
           const float be = beta[b], nb2 = -be * kLog2e, mx2 = nb2 * dmin, w = wl[b * 64];
-          float s = 0.f, ex = 0.f, ey = 0.f, ed = 0.f;
+          float s2[2] = {}, ex2[2] = {}, ey2[2] = {}, ed2[2] = {};   // even and odd headings
 #pragma unroll
           for (int k = 0; k < KM; ++k) {
             const float p = fast_exp2(fmaf(nb2, dl[k], -mx2));
-            s += p;
-            ex = fmaf(p, ux[k], ex);
-            ey = fmaf(p, uy[k], ey);
-            ed = fmaf(p, dl[k] - dls, ed);
+            s2[k & 1] += p;
+            ex2[k & 1] = fmaf(p, ux[k], ex2[k & 1]);
+            ey2[k & 1] = fmaf(p, uy[k], ey2[k & 1]);
+            ed2[k & 1] = fmaf(p, dl[k] - dmin, ed2[k & 1]);
           }
-          const float inv = 1.f / s;
-          // E[yhat] - yhat_* = ex/s ; E[Delta] - Delta_* = ed/s
-          agx -= (double)(w * (be * (ex * inv)));
-          agy -= (double)(w * (be * (ey * inv)));
-          ab[b * nthr] += (double)(w * (be * (ed * inv)));
+          const float inv = 1.f / (s2[0] + s2[1]);
+          // E[yhat] - yhat_* = ex/s ; E[Delta - min] - (Delta_* - min) = ed/s - ...
+          agx -= (double)(w * (be * ((ex2[0] + ex2[1]) * inv)));
+          agy -= (double)(w * (be * ((ey2[0] + ey2[1]) * inv)));
+          ab[b * nthr] += (double)(w * (be * fmaf(ed2[0] + ed2[1], inv, dmin - dls)));
         }
       } else {
         // any K: per (beta, heading), without per-heading arrays beyond dl and dk
