@@ -10,10 +10,10 @@
 // a step -- FP64 sine and cosine, the grid read, the cost -- needs no other
 // step's.  So the waves stage the controls, two waves run the sums of v and
 // theta through LDS, all waves take their steps' sine and cosine, two waves run
-// x and y, all waves take their steps' costs, and one wave adds those in step
-// order, so that a sample's cost depends neither on the batch nor on the waves
-// (perturbations laid out [T][N][2]: a wave reads 64 consecutive (a, omega) pairs
-// per step).  The robot state and the cost run in FP64: the collision term is a
+// x and y, and all waves add their steps' costs, always by the step's place among
+// 16, which one wave sums in order: a sample's cost depends neither on the batch nor
+// on the waves (perturbations laid out [T][N][2]: a wave reads 64 consecutive
+// (a, omega) pairs per step).  The robot state and the cost run in FP64: the collision term is a
 // step function of the grid cell, and FP64 positions (every product and sum
 // rounded on its own) keep the cell decisions of this kernel and of an FP64
 // reference identical
@@ -27,6 +27,7 @@
 namespace capred {
 
 constexpr int kChunkSteps = 48;        // steps of a chunk (3 per wave at 16 waves)
+constexpr int kRuns = 16;              // partial costs of a chunk: steps r, r + 16, r + 32
 constexpr int kUpdateThreads = 1024;
 
 struct MppiArgs {
@@ -48,16 +49,23 @@ template <int W>
 __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) {
 #pragma clang fp contract(off)
   constexpr int kOwn = kChunkSteps / W;   // steps of a wave per chunk
-  static_assert(kChunkSteps % W == 0 && W >= 2, "a chunk is whole steps per wave");
-  static_assert(kChunkSteps % 16 == 0, "the costs are summed 16 steps at a time");
+  static_assert(kChunkSteps % kRuns == 0 && kRuns % W == 0 && W >= 3, "whole runs per wave");
+  constexpr int kOwnRuns = kRuns / W;     // runs wave, wave + W, ... of a chunk
   // row t + 1 belongs to step t of the chunk, row 0 to the state before it
   __shared__ double A[kChunkSteps + 1][64], B[kChunkSteps + 1][64];
+  __shared__ double part[kRuns][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
   const int is = min(i, a.N - 1);   // lanes past the end repeat the last sample
   const double2* dl = reinterpret_cast<const double2*>(a.delta);
   const size_t plane = (size_t)a.nx * a.ny;
-  double sum = 0.0;   // wave 0: the sample's cost so far
+  // The last wave carries the cost: it adds a chunk's runs while the first two run
+  // the next chunk's sums (part is written again some barriers later).
+  double sum = 0.0;
+  const auto add_runs = [&] {
+#pragma unroll 8
+    for (int r = 0; r < kRuns; ++r) sum += part[r][lane];
+  };
   double c0 = wave == 0 ? a.z0[2] : a.z0[3];   // wave 0 carries v and x, wave 1 theta and y
   double c1 = wave == 0 ? a.z0[0] : a.z0[1];
   for (int t0 = 0; t0 < a.T; t0 += kChunkSteps) {
@@ -75,6 +83,7 @@ __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) 
       }
     }
     __syncthreads();
+    if (wave == W - 1 && t0 > 0) add_runs();
     if (wave < 2) {
       double (*R)[64] = wave == 0 ? A : B;
       R[0][lane] = c0;
@@ -126,53 +135,44 @@ __global__ void __launch_bounds__(64 * W) mppi_rollout_kernel(const MppiArgs a) 
         y[k] = B[t + 1][lane];
       }
     }
-    // (A from here on: each step's cost, in the row that its wave alone read)
+    // (no barrier: the next chunk's rows are written by the waves that read these)
+    double s[kOwnRuns] = {};
 #pragma unroll
     for (int k = 0; k < kOwn; ++k) {
       const int t = t0 + wave + k * W + 1;   // 1 .. T
       if (wave + k * W < tn) {
-        double s = 0.0;
         const double e0 = x[k] - a.goal[0], e1 = y[k] - a.goal[1], e2 = v[k] - a.goal[2],
                      e3 = th[k] - a.goal[3];
         if (t < a.T) {
-          s += a.Q[0] * e0 * e0;
-          s += a.Q[1] * e1 * e1;
-          s += a.Q[2] * e2 * e2;
-          s += a.Q[3] * e3 * e3;
-          s += a.R[0] * ua[k] * ua[k] + a.R[1] * uw[k] * uw[k];
+          s[k % kOwnRuns] += a.Q[0] * e0 * e0;
+          s[k % kOwnRuns] += a.Q[1] * e1 * e1;
+          s[k % kOwnRuns] += a.Q[2] * e2 * e2;
+          s[k % kOwnRuns] += a.Q[3] * e3 * e3;
+          s[k % kOwnRuns] += a.R[0] * ua[k] * ua[k] + a.R[1] * uw[k] * uw[k];
           if (a.occ && t <= a.H) {
             const double cx = floor((x[k] - a.x0) / a.cell), cy = floor((y[k] - a.y0) / a.cell);
             if (cx >= 0.0 && cx < (double)a.nx && cy >= 0.0 && cy < (double)a.ny) {
               const float p = a.occ[(size_t)(t - 1) * plane + (size_t)cy * a.nx + (size_t)cx];
-              if ((double)p >= a.p_coll) s += a.w_coll;
+              if ((double)p >= a.p_coll) s[k % kOwnRuns] += a.w_coll;
             }
           }
-          s += a.c_time;
+          s[k % kOwnRuns] += a.c_time;
         } else {
-          s += a.Qf[0] * e0 * e0;
-          s += a.Qf[1] * e1 * e1;
-          s += a.Qf[2] * e2 * e2;
-          s += a.Qf[3] * e3 * e3;
+          s[k % kOwnRuns] += a.Qf[0] * e0 * e0;
+          s[k % kOwnRuns] += a.Qf[1] * e1 * e1;
+          s[k % kOwnRuns] += a.Qf[2] * e2 * e2;
+          s[k % kOwnRuns] += a.Qf[3] * e3 * e3;
         }
-        A[wave + k * W + 1][lane] = s;
-      } else {
-        A[wave + k * W + 1][lane] = 0.0;   // up to whole batches of the sum below
       }
     }
-    __syncthreads();
-    if (wave == 0) {
-      constexpr int kBatch = 16;   // reads in flight together
-      for (int t = 1; t <= tn; t += kBatch) {
-        double c[kBatch];
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) c[k] = A[t + k][lane];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) sum += c[k];
-      }
-    }
-    if (t0 + kChunkSteps < a.T) __syncthreads();   // the next chunk rewrites A and B
+    for (int j = 0; j < kOwnRuns; ++j) part[wave + j * W][lane] = s[j];
   }
-  if (wave == 0 && i < a.N) a.S[i] = sum;
+  __syncthreads();
+  if (wave == W - 1) {
+    add_runs();
+    if (i < a.N) a.S[i] = sum;
+  }
 }
 
 // Block-wide reduction of M values in a fixed order (a butterfly in each wave,
@@ -214,8 +214,9 @@ __global__ void __launch_bounds__(kUpdateThreads)
   double acc[3] = {0.0, 0.0, 0.0};   // sum w, sum w delta
   const double2* dl = reinterpret_cast<const double2*>(delta) + (size_t)t * N;
   // (m - S) / tau as a product with the rounded reciprocal and one correction,
-  // which rounds as the division does (Markstein); out of its range, and for
-  // exponents whose weight is 0, the division and the product themselves.
+  // which rounds as the division does (Markstein); out of the range of tau where
+  // nothing over- or underflows, the division itself.  The bound (its weight is 0
+  // already) keeps an infinite cost from a product of infinities; NaN stays NaN.
   const double rate = 1.0 / tau;
   const auto add = [&](auto quotient) {
 #pragma unroll 8
@@ -229,8 +230,8 @@ __global__ void __launch_bounds__(kUpdateThreads)
   };
   if (tau > 0x1p-500 && tau < 0x1p500)
     add([&](double x) {
-      const double q = x * rate;
-      return q > -4096.0 ? fma(fma(-q, tau, x), rate, q) : q;
+      const double q = fmax(x * rate, -4096.0);
+      return fma(fma(-q, tau, x), rate, q);
     });
   else
     add([&](double x) { return x / tau; });

@@ -50,3 +50,22 @@ def test_extreme_temperatures(cap, tau):
     else:             # equal weights; 300 additions of terms near 1
         want = U0 + delta.mean(1)
         assert torch.max((U - want).abs()).item() < 300 * 2.0 ** -53 * 4
+
+
+def test_infinite_and_undefined_costs(cap):
+    """A sample whose cost is infinite has weight 0; a NaN cost makes the controls NaN."""
+    T, N = 5, 200
+    g = torch.Generator(device="cuda").manual_seed(2)
+    delta = torch.randn((T, N, 2), generator=g, device="cuda", dtype=torch.float64)
+    some = delta.clone()
+    some[1, 100:, 0] = 1e200            # cost overflows
+    S, U, U0 = costs(cap, some, T)
+    assert torch.isinf(S[100:]).all() and torch.isfinite(S[:100]).all()
+    w = torch.exp((S[:100].min() - S[:100]) / 20.0)
+    d = delta[:, :100]
+    want = U0 + (w[None, :, None] * d).sum(1) / w.sum()
+    keep = torch.tensor([0, 2, 3, 4], device="cuda")
+    assert torch.max((U - want)[keep].abs()).item() < 100 * 2.0 ** -53 * 8
+    some[1, 150, 0] = float("nan")
+    _, U, _ = costs(cap, some, T)
+    assert torch.isnan(U).all()
