@@ -175,10 +175,11 @@ static cap_status launch_plain_t(const RolloutDesc& d, uint32_t slo, uint32_t sh
 }
 
 // Shape of the launch.  Few particles are bound by the latency of a step, which
-// a block of one wave keeps shortest, so blocks grow (64 threads at a time)
-// only as far as one block per CU asks.  Many particles are bound by the
-// device-scope atomics of the flush: a tile adds each cell it touched once per
-// step, so larger tiles add less.  2^18 particles x 50 steps (K = 16): 1024
+// a block of one wave keeps shortest while one per CU holds them all.  More are
+// bound by the device-scope atomics of the flush: a tile adds each cell it touched
+// once per step, so larger tiles add less: from two waves per CU on blocks of four
+// (30000 particles x 23 steps, K = 8: 128 threads 53.3 us, 256 threads 49.8), then as
+// many as one block per CU asks.  2^18 particles x 50 steps (K = 16): 1024
 // blocks of 256 threads issue 4.75e6 atomics and the call takes 337-378 us, with
 // 256 blocks of 1024 threads 214; 8192 particles x 10 steps (96 controls): 32
 // blocks of 256 threads 73.9 us, 128 of 64 threads 69.0.
@@ -199,6 +200,7 @@ template <int KT, bool MS>
 static cap_status launch_plain_k(const RolloutDesc& d, int64_t cus, uint32_t slo, uint32_t shi,
                                  hipStream_t s) {
   const int64_t waves = (d.N + 64 * cus - 1) / (64 * cus);   // per CU
+  const int64_t blk = waves == 1 ? 1 : std::max<int64_t>(waves, 4);
   int most = 1024;
   if constexpr (MS) {
     // few particles: several lanes each, eight while those fit two waves per SIMD, then
@@ -222,7 +224,7 @@ static cap_status launch_plain_k(const RolloutDesc& d, int64_t cus, uint32_t slo
     else if (waves > 32) return launch_plain_t<KT, 4, MS>(d, slo, shi, 1024, s);
     else if (waves > 16) return launch_plain_t<KT, 2, MS>(d, slo, shi, 1024, s);
   }
-  return launch_plain_t<KT, 1, MS>(d, slo, shi, (int)std::min<int64_t>(64 * waves, most), s);
+  return launch_plain_t<KT, 1, MS>(d, slo, shi, (int)std::min<int64_t>(64 * blk, most), s);
 }
 
 static cap_status launch_plain(RolloutDesc& d, uint32_t slo, uint32_t shi, hipStream_t s) {
