@@ -314,17 +314,19 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
   if constexpr (L > 1) rows.load(ctl, d.S, tid % L);
   // The descriptor's fields that every step reads, in scalar registers for the
   // whole tile: it lies in memory that the loop's stores could alias, so each
-  // use would be a load and a wait.  Several speeds read them from there: their
-  // controls' table fills the scalar registers, and what is held besides goes to
-  // vector-register lanes, one VALU access each (K = 16: 55 more a step; 16 humans
-  // x 30000 particles of 6 x 16 controls, 30 steps: 782 us read, 823 held).
-  using Int = std::conditional_t<MS, const int32_t&, const int32_t>;
+  // use would be a load and a wait.  Several speeds by one lane read them from
+  // there: their controls' table fills the scalar registers, and what is held
+  // besides goes to vector-register lanes, one VALU access each (K = 16: 55 more a
+  // step; 16 humans x 30000 particles of 6 x 16 controls, 30 steps: 782 us read, 823
+  // held).
+  constexpr bool kRead = MS && L == 1;
+  using Int = std::conditional_t<kRead, const int32_t&, const int32_t>;
   Int H = d.H, nx = d.nx, ny = d.ny, Rx = d.Rx, Ry = d.Ry, S = d.S, s_last = d.s_last;
-  std::conditional_t<MS, const uint32_t&, const uint32_t> human = d.human, smask = d.smask;
-  std::conditional_t<MS, uint32_t* const&, uint32_t* const> counts = d.counts;
-  std::conditional_t<MS, uint8_t* const&, uint8_t* const> trace_k = d.trace_k;
+  std::conditional_t<kRead, const uint32_t&, const uint32_t> human = d.human, smask = d.smask;
+  std::conditional_t<kRead, uint32_t* const&, uint32_t* const> counts = d.counts;
+  std::conditional_t<kRead, uint8_t* const&, uint8_t* const> trace_k = d.trace_k;
   const FarConst fc = d.far;
-  const size_t plane = MS ? 0 : (size_t)nx * (size_t)ny;   // (several speeds: each step's own)
+  const size_t plane = kRead ? 0 : (size_t)nx * (size_t)ny;   // (read: each step's own)
   uint4 rw[P];
   const int list_cap = P * nthr;
   int m3 = 1;  // t mod 3
@@ -390,7 +392,7 @@ __device__ __forceinline__ void rollout_tile_body(const RolloutDesc& d, int64_t 
     uint16_t* list = single ? lists : lists + (t & 1) * list_cap;
     // both buffers: the previous step's flush (of either buffer) must be over
     if (single) __syncthreads();
-    uint32_t* grid_t = counts + (size_t)(t - 1) * (MS ? (size_t)nx * (size_t)ny : plane);
+    uint32_t* grid_t = counts + (size_t)(t - 1) * (kRead ? (size_t)nx * (size_t)ny : plane);
     // Draws of all P particles first, then their emplacement: the draws are
     // independent dependency chains (transcendental latency), which the
     // scheduler can interleave only while no branch separates them.  Each
