@@ -75,7 +75,9 @@ __host__ __device__ inline int smooth_tiles(int ny, int nx) {
 // written per cell, the halo from cache); the halo of a 64 x 32 tile costs
 // 1.3 x the reads at RM = 3.  100 x 256 x 256 cells at r = 3: 19.4 us, 2.7 TB/s
 // of reads and writes (75 us with a thread per column that read each tap from
-// memory, one row after another; 10 x 50 x 50 cells: 6.6 us, before 45.6).
+// memory, one row after another; 10 x 50 x 50 cells: 6.6 us, before 45.6).  Rows off
+// the grid are zeros without their sums (50 x 3 x 2000 cells at r = 9: 17.3 us with
+// them, 11.4 without).
 // Every thread of the block must call it; the caller separates two calls that
 // reuse `tile` with another barrier.  un (nullable): that step's plane of a
 // union grid of the same frame, raised to each nonzero output by an integer
@@ -101,6 +103,10 @@ __device__ __forceinline__ void smooth_block(const uint32_t* __restrict__ c,
   __syncthreads();
   for (int i = tid; i < T::kRows * (kBandCols / 4); i += kSmoothThreads) {
     const int row = i / (kBandCols / 4), q = i - row * (kBandCols / 4);
+    if (y0 - RM + row < 0 || y0 - RM + row >= ny) {   // off the grid: zeros
+      reinterpret_cast<float4*>(hx + row * kBandCols)[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+      continue;
+    }
     float v[4 + 2 * T::kHalo];
     const float4* src = reinterpret_cast<const float4*>(in + row * T::kPitch) + q;
 #pragma unroll
